@@ -732,11 +732,11 @@ struct UnionParts {
 
 // The same union, partitioned: the blocks of both rows first, then those of
 // row0 only, then those of row0 + 1 only, each part in ascending j (entries
-// j | membership << 16 as above).  wsum holds 2 * NT/64 ints.
+// j alone: the part says which rows hold it).  wsum holds 2 * NT/64 ints.
 template <int NT>
 __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv_idx,
                                                   const int32_t* __restrict__ kv_cnt, size_t row0, bool has1,
-                                                  int n, uint8_t* umask, uint32_t* ulist, int* wsum, int tid,
+                                                  int n, uint8_t* umask, uint16_t* ulist, int* wsum, int tid,
                                                   int lane, int w) {
     constexpr int JPT = kMaxBlocks / NT;
     mark_rows<NT>(kv_idx, kv_cnt, row0, has1, n, umask, tid);
@@ -785,7 +785,7 @@ __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv
     for (int e = 0; e < JPT; ++e) {
         const int j = tid * JPT + e;
         const int u = j < n ? umask[j] : 0;
-        const uint32_t ent = (uint32_t)j | ((uint32_t)u << 16);
+        const uint16_t ent = (uint16_t)j;
         if (u == 3) ulist[p3++] = ent;
         if (u == 1) ulist[p1++] = ent;
         if (u == 2) ulist[p2++] = ent;
@@ -793,8 +793,18 @@ __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv
     return r;
 }
 
+// Work-groups resident on a compute unit at once.  A work-group of 64-row
+// blocks has four waves, one per SIMD, which by itself leaves every phase's
+// latency exposed; its four tile buffers (64 KB at D = 128, 32 KB at D = 64)
+// and the 8 KB union list leave LDS for two or three.  Measured at 24 heads,
+// 35,200 tokens, d = 128, 64-token blocks, 20% kept: 4.63 ms with one group
+// per unit, 3.65 ms with two (0.72 -> 0.91 PFLOP/s on kept blocks).  128-row
+// blocks have two waves per SIMD already, and at D = 128 all registers.
 template <int D, int BS>
-__global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
+constexpr int kGroupsPerCu = BS == 128 ? 1 : (D == 128 ? 2 : 3);
+
+template <int D, int BS>
+__global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_fwd_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ kv_idx,
     const int32_t* __restrict__ kv_cnt, float scale, uint16_t* __restrict__ o,
@@ -817,8 +827,11 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     char* const kb1 = tiles + TILE;
     char* const vb0 = tiles + 2 * TILE;
     char* const vb1 = tiles + 3 * TILE;
-    __shared__ uint32_t ulist[kMaxBlocks];     // union of the two lists: j | membership << 16
-    __shared__ uint8_t umask[kMaxBlocks];
+    __shared__ uint16_t ulist[kMaxBlocks];     // union of the two lists, by part
+    // the membership bytes of the union build, in a tile buffer (no copy into
+    // it is under way between two items)
+    static_assert(TILE >= kMaxBlocks, "the membership bytes must fit one tile buffer");
+    uint8_t* const umask = reinterpret_cast<uint8_t*>(kb0);
     __shared__ int wsum[2 * NT / 64];
     __shared__ int item_s[4];          // pair, first step, end step, slot (-1: whole pair)
 
@@ -1138,7 +1151,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     uint32_t e_nxt = t0 + 1 < t1 ? ulist[t0 + 1] : 0u;
     e_cur = __builtin_amdgcn_readfirstlane(e_cur);
     e_nxt = __builtin_amdgcn_readfirstlane(e_nxt);
-    if (t0 < t1) copy.issue_all(g == 0 ? kg : vg, (int)(e_cur & 0xFFFF), L, g == 0 ? kb0 : vb0, qw, lane);
+    if (t0 < t1) copy.issue_all(g == 0 ? kg : vg, (int)e_cur, L, g == 0 ? kb0 : vb0, qw, lane);
     // Q and the first tile are complete before the tile loop: no wait on
     // the memory counter (which also counts the tile copies) is left for the
     // loop to inherit.
@@ -1171,7 +1184,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     char* vp = vb1;
     auto tile = [&](int t) __attribute__((always_inline)) {
         const bool more = t + 1 < t1;
-        const int jc = (int)(e_cur & 0xFFFF), jn = (int)(e_nxt & 0xFFFF);
+        const int jc = (int)e_cur, jn = (int)e_nxt;
         const int kvalid = min(BS, L - jc * BS);
         // first half: S from K(t) rows [0, KVW); product of V(t-1) rows [KVW, BS)
         mphase(IC0{}, ICH{});
@@ -1219,7 +1232,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     if (x1 > x0) {
         barrier();   // group 1's last product of the shared part has read its buffers
         const int cgx = min(g == 0 ? na : nb, x1);   // this group's end of the walk
-        const uint32_t* el = ulist + (g == 0 ? ns : ns + na);
+        const uint16_t* el = ulist + (g == 0 ? ns : ns + na);
         char* kbuf = g == 0 ? kb0 : kb1;
         char* vbuf = g == 0 ? vb0 : vb1;
         constexpr int IPH = Copy::IPH;
@@ -1232,8 +1245,8 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
             // the first product multiplies P = 0 with this half: zeros, not stale LDS
             for (int e = 64 * qw + lane; e < HALF / 16; e += 64 * QW)
                 reinterpret_cast<uint4*>(vbuf + HALF)[e] = make_uint4(0, 0, 0, 0);
-            copy.issue_all(kg, (int)(ec & 0xFFFF), L, kbuf, qw, lane);
-            copy.issue_half(vg, (int)(ec & 0xFFFF), L, vbuf, 0, qw, lane);
+            copy.issue_all(kg, (int)ec, L, kbuf, qw, lane);
+            copy.issue_half(vg, (int)ec, L, vbuf, 0, qw, lane);
         }
         wait_copies();
         barrier();
@@ -1282,7 +1295,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
         for (int x = x0; x < x1; ++x) {
             const bool active = x < cgx;
             const bool more = x + 1 < cgx;
-            const int jc = (int)(ec & 0xFFFF), jn = (int)(en & 0xFFFF);
+            const int jc = (int)ec, jn = (int)en;
             const int kvalid = min(BS, L - jc * BS);
             // first half: S from K(x) rows [0, KVW); product of V(x-1) rows [KVW, BS)
             mphase_if(kbuf, vbuf + HALF, active, prev_active);
@@ -1364,9 +1377,10 @@ hipError_t launch(const uint16_t* q, const uint16_t* k, const uint16_t* v, const
                   const int32_t* kv_cnt, float scale, uint16_t* o, float* lse, int BH, int L, int n,
                   void* ws, int S, hipStream_t s) {
     const int ncu = persistent_groups();
-    hipLaunchKernelGGL(plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, ncu, S);
+    const int slots = ncu * kGroupsPerCu<D, BS>;   // work-groups resident at once
+    hipLaunchKernelGGL(plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
     const long items = (long)BH * ((n + 1) / 2) + S;
-    const unsigned groups = (unsigned)std::min<long>(ncu, items);
+    const unsigned groups = (unsigned)std::min<long>(slots, items);
     hipLaunchKernelGGL((attn_fwd_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
                        q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
     if (S > 0)

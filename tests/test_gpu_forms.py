@@ -1,0 +1,63 @@
+"""GPU parity of the attention's (head width, block size) forms where the
+launch differs between them, against the oracle.
+
+Each form keeps a different number of work-groups on a compute unit and
+fetches further items once its first is done: layers with more (head, pair)
+items than groups resident at once, uneven random lists (empty, full, short
+and long rows), a short tail block, sampled query blocks.
+"""
+import math
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from parity import LSE_ABS, MAX_ABS, MEAN_ABS, attention_errors, bf16_tensor, bf16_to_f64
+
+import paper_2601_11641_amd as M
+from test_gpu_parity import _uneven_lists
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def _layer(B, H, L, d, seed, spread=1.5):
+    """N(0, 1) values, Q and K scaled by spread, as bf16 bits and tensors."""
+    rng = np.random.default_rng(seed)
+    host = [W.to_bf16_bits(rng.standard_normal((B, H, L, d)).astype(np.float32) * (spread if t < 2 else 1.0))
+            for t in range(3)]
+    return host, tuple(bf16_tensor(x) for x in host)
+
+
+def _check_rows(host, rows, o, lse, d, bs, L, heads, sample):
+    scale = 1.0 / math.sqrt(d)
+    og, lg = bf16_to_f64(o), lse.cpu().numpy().astype(np.float64)
+    for b, h in heads:
+        qf, kf, vf = (W.bf16_bits_to_f64(x[b, h]) for x in host)
+        Oo, Lo = O.attention(qf, kf, vf, rows[b][h], bs, scale, rows=sample)
+        for i in sample:
+            sl = slice(i * bs, min(L, (i + 1) * bs))
+            mx, mean = attention_errors(og[b, h, sl], Oo[sl])
+            assert mx <= MAX_ABS and mean <= MEAN_ABS, (b, h, i, mx, mean)
+            fin = np.isfinite(Lo[sl])
+            assert (np.isneginf(lg[b, h, sl]) == ~fin).all(), (b, h, i)
+            if fin.any():
+                assert np.abs(lg[b, h, sl][fin] - Lo[sl][fin]).max() <= LSE_ABS, (b, h, i)
+
+
+@pytest.mark.parametrize("d,bs,tail", [(128, 128, 1), (128, 64, 63), (64, 128, 37), (64, 64, 16)])
+def test_attention_more_items_than_resident_groups(d, bs, tail):
+    B, H, n = 2, 9, 101       # 18 heads x 51 pairs, the last of one block
+    L = (n - 1) * bs + tail
+    host, (q, k, v) = _layer(B, H, L, d, 100 + d + bs)
+    rows, idx, cnt = _uneven_lists(B, H, n, 7)
+    shape = M.make_shape(B, H, L, d, bs)
+    for ws_bytes in (M.mod_attn_workspace_bytes(shape), M.mod_attn_plan_bytes(shape)):
+        ws = torch.zeros(ws_bytes, dtype=torch.uint8, device="cuda")
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((B, H, L), float("nan"), dtype=torch.float32, device="cuda")
+        M.mod_block_sparse_attn_fwd(shape, q, k, v, idx, cnt, 0.0, o, lse, ws, ws_bytes)
+        assert not torch.isnan(o.float()).any() and not torch.isnan(lse).any()
+        _check_rows(host, rows, o, lse, d, bs, L, [(0, 0), (0, 8), (1, 4)], [0, 1, 2, 49, 50, 98, 99, 100])
