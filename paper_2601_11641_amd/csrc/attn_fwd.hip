@@ -1,5 +1,9 @@
 // Block-sparse attention forward for gfx950 (Eq. 1 with a block mask).
 //
+// Two kernels: attn_fwd_kernel for d = 128 with 128-row blocks, described
+// here, and attn_narrow_kernel for the smaller tiles (d = 64 or 64-row
+// blocks), which shares its work items, lists and operand layouts.
+//
 // One work item per (head, pair of query blocks 2p, 2p+1), processed by a
 // persistent work-group (one per compute unit, items fetched from a work
 // plan written before the launch) with 2 * BS/32 waves in two groups: group g
@@ -70,10 +74,12 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // one); its completion is tracked by vmcnt alone and waited for explicitly
 // before the barrier that publishes the tile.  M0 carries the LDS address;
 // nothing else in this kernel uses M0.
-__device__ __forceinline__ void lds_copy16(const void* sbase, uint32_t voff, const char* lds) {
-    const uint32_t m0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
+__device__ __forceinline__ void lds_copy16_at(const void* sbase, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(voff), "s"(sbase), "s"(m0) : "memory");
+                 :: "v"(voff), "s"(sbase), "s"(lds) : "memory");
+}
+__device__ __forceinline__ void lds_copy16(const void* sbase, uint32_t voff, const char* lds) {
+    lds_copy16_at(sbase, voff, (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds);
 }
 
 // XOR pattern applied to the 16-byte chunk index of a tile row.  The LDS
@@ -648,6 +654,28 @@ __device__ __forceinline__ int fetch_item(const Plan& pl, int x) {
     return -1;
 }
 
+// The next item of this work-group into item_s = {pair, first step, end
+// step, slot (-1: whole pair)}; pair -1 ends the work-group, -2 is skipped.
+// One thread calls it.  (attn_fwd_kernel spells the same steps out: called
+// from there, the function cost 0.8% at 720p through another register
+// assignment.)
+__device__ __forceinline__ void take_item(void* ws, int BH, int npairs, int S, int* item_s) {
+    const Plan pl(ws, BH, npairs, S);
+    const int it = fetch_item(pl, blockIdx.x % kXcds);
+    int4 desc = make_int4(it, 0, 0x7fffffff, -1);
+    if (it >= 0 && (it & kChunkBit)) {
+        const int k2 = it & (kChunkBit - 1);
+        desc = k2 < S ? pl.chunks[k2] : make_int4(-2, 0, 0, 0);
+        desc.w = k2;
+    }
+    // an item outside the plan's range is skipped (never read past the lists)
+    if (desc.x >= 0 && (long long)desc.x >= (long long)BH * npairs) desc.x = -2;
+    item_s[0] = desc.x;
+    item_s[1] = desc.y;
+    item_s[2] = desc.z;
+    item_s[3] = desc.w;
+}
+
 // Membership bytes umask[j] of the kv lists of rows row0 and row0 + 1 (the
 // second only if has1) of the [rows, n] lists: bit 0 row0, bit 1 row0 + 1.
 // Counts are clamped to [0, n] (a row never reads past its n entries),
@@ -732,11 +760,11 @@ struct UnionParts {
 
 // The same union, partitioned: the blocks of both rows first, then those of
 // row0 only, then those of row0 + 1 only, each part in ascending j (entries
-// j alone: the part says which rows hold it).  wsum holds 2 * NT/64 ints.
-template <int NT>
+// j | membership << 16, or j alone where Entry has 16 bits).  wsum holds 2 * NT/64 ints.
+template <int NT, class Entry>
 __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv_idx,
                                                   const int32_t* __restrict__ kv_cnt, size_t row0, bool has1,
-                                                  int n, uint8_t* umask, uint16_t* ulist, int* wsum, int tid,
+                                                  int n, uint8_t* umask, Entry* ulist, int* wsum, int tid,
                                                   int lane, int w) {
     constexpr int JPT = kMaxBlocks / NT;
     mark_rows<NT>(kv_idx, kv_cnt, row0, has1, n, umask, tid);
@@ -785,7 +813,7 @@ __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv
     for (int e = 0; e < JPT; ++e) {
         const int j = tid * JPT + e;
         const int u = j < n ? umask[j] : 0;
-        const uint16_t ent = (uint16_t)j;
+        const Entry ent = (Entry)((uint32_t)j | ((uint32_t)u << 16));
         if (u == 3) ulist[p3++] = ent;
         if (u == 1) ulist[p1++] = ent;
         if (u == 2) ulist[p2++] = ent;
@@ -793,18 +821,58 @@ __device__ __forceinline__ UnionParts union_parts(const int32_t* __restrict__ kv
     return r;
 }
 
-// Work-groups resident on a compute unit at once.  A work-group of 64-row
-// blocks has four waves, one per SIMD, which by itself leaves every phase's
-// latency exposed; its four tile buffers (64 KB at D = 128, 32 KB at D = 64)
-// and the 8 KB union list leave LDS for two or three.  Measured at 24 heads,
-// 35,200 tokens, d = 128, 64-token blocks, 20% kept: 4.63 ms with one group
-// per unit, 3.65 ms with two (0.72 -> 0.91 PFLOP/s on kept blocks).  128-row
-// blocks have two waves per SIMD already, and at D = 128 all registers.
+// A lane's part of its query row: O^T in oacc (column l32 of the wave's 32
+// rows, rows 8 gq + 4 h + 0..3 of every 32-row d-tile), its running max m and
+// row sum l.  slot < 0: O / l in bf16 and the row's LSE; else a chunk of a
+// split pair: O / l in fp32 and the chunk's LSE into its slot.
 template <int D, int BS>
-constexpr int kGroupsPerCu = BS == 128 ? 1 : (D == 128 ? 2 : 3);
+__device__ __forceinline__ void store_row(const f32x16 (&oacc)[D / 32], float m, float l, float scale, int slot,
+                                          int g, int qw, int l32, int h, size_t base, int bh, int qrow, int L,
+                                          uint16_t* __restrict__ o, float* __restrict__ lse, void* ws, int BH,
+                                          int npairs, int S) {
+    constexpr int DT = D / 32;
+    if (slot >= 0) {
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        float* sl = Plan(ws, BH, npairs, S).part + (size_t)slot * slot_floats(D, BS);
+        float* prow = sl + ((size_t)g * BS + 32 * qw + l32) * D;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq)
+                *reinterpret_cast<float4*>(prow + 32 * dt + 8 * gq + 4 * h) =
+                    make_float4(oacc[dt][4 * gq] * inv, oacc[dt][4 * gq + 1] * inv, oacc[dt][4 * gq + 2] * inv,
+                                oacc[dt][4 * gq + 3] * inv);
+        if (h == 0) sl[2 * BS * D + g * BS + 32 * qw + l32] = l > 0.0f ? m * scale + logf(l) : -INFINITY;
+    } else {
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        uint16_t* orow = o + base + (size_t)qrow * D;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                uint16_t vals[4];
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr)
+                    vals[rr] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(oacc[dt][4 * gq + rr] * inv));
+                uint2 pk;
+                pk.x = (uint32_t)vals[0] | ((uint32_t)vals[1] << 16);
+                pk.y = (uint32_t)vals[2] | ((uint32_t)vals[3] << 16);
+                *reinterpret_cast<uint2*>(orow + 32 * dt + 8 * gq + 4 * h) = pk;
+            }
+        if (lse != nullptr && h == 0)
+            lse[(size_t)bh * L + qrow] = l > 0.0f ? m * scale + logf(l) : -INFINITY;
+    }
+}
+
+// Work-groups resident on a compute unit at once: one of attn_fwd_kernel
+// (139 KB of LDS, all registers), and of attn_narrow_kernel as many as its
+// tile buffers and the 8 KB union list allow (72 KB at 128 x 64 and 64 x 128:
+// two; 40 KB at 64 x 64: four).
+template <int D, int BS>
+constexpr int kGroupsPerCu = D * BS == 128 * 128 ? 1 : (D * BS == 64 * 64 ? 4 : 2);
 
 template <int D, int BS>
-__global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_fwd_kernel(
+__global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ kv_idx,
     const int32_t* __restrict__ kv_cnt, float scale, uint16_t* __restrict__ o,
@@ -818,6 +886,7 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
     constexpr int TILE = BS * D * 2;   // bytes per K or V tile
     constexpr int ROWB = 2 * D;
     constexpr int HALF = KVW * ROWB;   // bytes per half tile
+    static_assert(D == 128 && BS == 128, "other tiles: attn_narrow_kernel");
     using Copy = TileCopy<D, BS, QW>;
     constexpr int IPW = Copy::IPW;
     // K and V tile buffers, at fixed distances: the matrix-phase reads name
@@ -827,11 +896,8 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
     char* const kb1 = tiles + TILE;
     char* const vb0 = tiles + 2 * TILE;
     char* const vb1 = tiles + 3 * TILE;
-    __shared__ uint16_t ulist[kMaxBlocks];     // union of the two lists, by part
-    // the membership bytes of the union build, in a tile buffer (no copy into
-    // it is under way between two items)
-    static_assert(TILE >= kMaxBlocks, "the membership bytes must fit one tile buffer");
-    uint8_t* const umask = reinterpret_cast<uint8_t*>(kb0);
+    __shared__ uint32_t ulist[kMaxBlocks];     // union of the two lists: j | membership << 16
+    __shared__ uint8_t umask[kMaxBlocks];
     __shared__ int wsum[2 * NT / 64];
     __shared__ int item_s[4];          // pair, first step, end step, slot (-1: whole pair)
 
@@ -1108,16 +1174,11 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
                     t1[6 * rt + gq] = fmaxf(sacc[rt][3 * gq], fmaxf(sacc[rt][3 * gq + 1], sacc[rt][3 * gq + 2]));
                 t1[6 * rt + 5] = sacc[rt][15];
             }
-            float mx;
-            if constexpr (RT == 2) {
-                const float u0 = fmaxf(t1[0], fmaxf(t1[1], t1[2]));
-                const float u1 = fmaxf(t1[3], fmaxf(t1[4], t1[5]));
-                const float u2 = fmaxf(t1[6], fmaxf(t1[7], t1[8]));
-                const float u3 = fmaxf(t1[9], fmaxf(t1[10], t1[11]));
-                mx = fmaxf(fmaxf(u0, u1), fmaxf(u2, u3));
-            } else {
-                mx = fmaxf(fmaxf(t1[0], fmaxf(t1[1], t1[2])), fmaxf(t1[3], fmaxf(t1[4], t1[5])));
-            }
+            const float u0 = fmaxf(t1[0], fmaxf(t1[1], t1[2]));
+            const float u1 = fmaxf(t1[3], fmaxf(t1[4], t1[5]));
+            const float u2 = fmaxf(t1[6], fmaxf(t1[7], t1[8]));
+            const float u3 = fmaxf(t1[9], fmaxf(t1[10], t1[11]));
+            float mx = fmaxf(fmaxf(u0, u1), fmaxf(u2, u3));
             mx = max_across_halves(mx);
             const float m_new = fmaxf(m, mx);
             const float alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * c2);
@@ -1151,7 +1212,7 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
     uint32_t e_nxt = t0 + 1 < t1 ? ulist[t0 + 1] : 0u;
     e_cur = __builtin_amdgcn_readfirstlane(e_cur);
     e_nxt = __builtin_amdgcn_readfirstlane(e_nxt);
-    if (t0 < t1) copy.issue_all(g == 0 ? kg : vg, (int)e_cur, L, g == 0 ? kb0 : vb0, qw, lane);
+    if (t0 < t1) copy.issue_all(g == 0 ? kg : vg, (int)(e_cur & 0xFFFF), L, g == 0 ? kb0 : vb0, qw, lane);
     // Q and the first tile are complete before the tile loop: no wait on
     // the memory counter (which also counts the tile copies) is left for the
     // loop to inherit.
@@ -1184,7 +1245,7 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
     char* vp = vb1;
     auto tile = [&](int t) __attribute__((always_inline)) {
         const bool more = t + 1 < t1;
-        const int jc = (int)e_cur, jn = (int)e_nxt;
+        const int jc = (int)(e_cur & 0xFFFF), jn = (int)(e_nxt & 0xFFFF);
         const int kvalid = min(BS, L - jc * BS);
         // first half: S from K(t) rows [0, KVW); product of V(t-1) rows [KVW, BS)
         mphase(IC0{}, ICH{});
@@ -1232,7 +1293,7 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
     if (x1 > x0) {
         barrier();   // group 1's last product of the shared part has read its buffers
         const int cgx = min(g == 0 ? na : nb, x1);   // this group's end of the walk
-        const uint16_t* el = ulist + (g == 0 ? ns : ns + na);
+        const uint32_t* el = ulist + (g == 0 ? ns : ns + na);
         char* kbuf = g == 0 ? kb0 : kb1;
         char* vbuf = g == 0 ? vb0 : vb1;
         constexpr int IPH = Copy::IPH;
@@ -1245,8 +1306,8 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
             // the first product multiplies P = 0 with this half: zeros, not stale LDS
             for (int e = 64 * qw + lane; e < HALF / 16; e += 64 * QW)
                 reinterpret_cast<uint4*>(vbuf + HALF)[e] = make_uint4(0, 0, 0, 0);
-            copy.issue_all(kg, (int)ec, L, kbuf, qw, lane);
-            copy.issue_half(vg, (int)ec, L, vbuf, 0, qw, lane);
+            copy.issue_all(kg, (int)(ec & 0xFFFF), L, kbuf, qw, lane);
+            copy.issue_half(vg, (int)(ec & 0xFFFF), L, vbuf, 0, qw, lane);
         }
         wait_copies();
         barrier();
@@ -1295,7 +1356,7 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
         for (int x = x0; x < x1; ++x) {
             const bool active = x < cgx;
             const bool more = x + 1 < cgx;
-            const int jc = (int)ec, jn = (int)en;
+            const int jc = (int)(ec & 0xFFFF), jn = (int)(en & 0xFFFF);
             const int kvalid = min(BS, L - jc * BS);
             // first half: S from K(x) rows [0, KVW); product of V(x-1) rows [KVW, BS)
             mphase_if(kbuf, vbuf + HALF, active, prev_active);
@@ -1321,38 +1382,335 @@ __global__ __launch_bounds__(BS * 4, (kGroupsPerCu<D, BS> * BS) / 64) void attn_
 
     // ---- output: this wave owns 32 complete query rows ----
     l += __shfl_xor(l, 32);
-    if (i < n && qrow < L && slot >= 0) {
-        // a chunk of a split pair: O / l in fp32 and the chunk's LSE into its slot
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        float* sl = Plan(wsi, BH, npairs, S).part + (size_t)slot * slot_floats(D, BS);
-        float* prow = sl + ((size_t)g * BS + 32 * qw + l32) * D;
+    if (i < n && qrow < L)
+        store_row<D, BS>(oacc, m, l, scale, slot, g, qw, l32, h, base, bh, qrow, L, o, lse, wsi, BH, npairs, S);
+    }   // next item
+}
+
+// ---------------------------------------------------------------------------
+// The forward for tiles under 32 KB (d = 64 or 64-row blocks): the same work
+// items, union lists, swizzled tiles and softmax step, without the ping-pong.
+//
+// At d = 64 a score costs as many vector instructions as at d = 128 but half
+// the matrix instructions (a 64 x 32 unit: ~720 cycles of vector issue against
+// 512 of products), so the vector unit bounds the kernel and a phase barrier
+// only adds waits; with 64-row blocks a work-group has one wave per SIMD, and
+// phases of half a tile are as short as their barriers.  Here a wave computes
+// a unit of 32 RT kv rows from start to end (scores, softmax step, product
+// with V), keeping no scores across units, which fits 128 registers at
+// d = 64: four waves share a SIMD there (two at d = 128) and cover each
+// other's matrix and LDS latencies.  Tiles are double-buffered, a whole tile
+// ahead in the shared part, half a tile in the exclusive part (where each
+// group has half of the buffers), with one barrier per tile or half tile.
+//
+// Measured at 20% kept blocks against attn_fwd_kernel in these forms (one
+// work-group per compute unit): d = 64, block 128, 2 x 30 heads, 29,666
+// tokens 3.50 -> 2.95 ms (0.97 PFLOP/s kept); d = 128, block 64, 24 heads,
+// 35,200 tokens 4.53 -> 3.10 ms (1.04 PFLOP/s; 3.65 ms with two ping-pong
+// groups per unit).  Counters at d = 64: vector unit busy 80% and matrix
+// cores 51% of the cycles, the clock power-limited; address arithmetic for
+// the operand reads, before their offset fields held it, cost 5%.
+// ---------------------------------------------------------------------------
+template <int D, int BS>
+constexpr int kNarrowWaves = D == 64 ? 4 : 2;   // waves per SIMD
+
+template <int D, int BS>
+__global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+    const uint16_t* __restrict__ v, const int32_t* __restrict__ kv_idx,
+    const int32_t* __restrict__ kv_cnt, float scale, uint16_t* __restrict__ o,
+    float* __restrict__ lse, int L, int n, void* ws, int BH, int S) {
+    constexpr int QW = BS / 32;        // waves per group
+    constexpr int NT = BS * 4;
+    constexpr int DT = D / 32;         // 32-row d tiles of O^T
+    constexpr int KK = D / 16;         // 16-deep d chunks of S^T
+    constexpr int ROWB = 2 * D;
+    constexpr int TILE = BS * ROWB;    // bytes per K or V tile
+    constexpr int LPR = ROWB / 16;     // lanes per row of a copy
+    constexpr int RPI = 64 / LPR;      // rows per 1-KB copy
+    constexpr int NV = 16 / RPI;       // copies per swizzle period = copies of a wave per tile or half tile
+    __shared__ __align__(1024) char tiles[4 * TILE];   // K, K, V, V
+    __shared__ uint16_t ulist[kMaxBlocks];
+    // the union build's scratch, in the first tile buffer (no copy into it is
+    // under way between two items)
+    uint8_t* const umask = reinterpret_cast<uint8_t*>(tiles);
+    int* const wsum = reinterpret_cast<int*>(tiles + kMaxBlocks);
+    int* const item_s = wsum + 2 * NT / 64;
+    static_assert(TILE >= kMaxBlocks + 256, "the union build's scratch must fit one tile buffer");
+    static_assert(TILE / 1024 == NV * 2 * QW, "each wave copies one swizzle period of a tile");
+
+    for (;;) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // per-item values are not hoisted out of the loop
+    const int npairs = (n + 1) / 2;
+    if (tid == 0) take_item(ws, BH, npairs, S, item_s);
+    __syncthreads();
+    const int item = item_s[0];
+    const int step0 = item_s[1], step1 = item_s[2], slot = item_s[3];
+    __syncthreads();
+    if (item == -1) break;
+    if (item < 0) continue;
+    const int bh = item / npairs, pr = item % npairs;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+    const int qw = w % QW, g = w / QW;
+    const int i = 2 * pr + g;
+    const size_t base = (size_t)bh * L * D;
+    const float c2 = scale * kLog2e;
+    const int qrow = i * BS + 32 * qw + l32;
+
+    const size_t row0 = (size_t)bh * n + 2 * pr;
+    const UnionParts parts = union_parts<NT>(kv_idx, kv_cnt, row0, 2 * pr + 1 < n, n, umask, ulist, wsum, tid, lane, w);
+    const int ns = parts.ns, na = parts.na, nb = parts.nb;
+
+    bf16x8 qreg[KK];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq)
-                *reinterpret_cast<float4*>(prow + 32 * dt + 8 * gq + 4 * h) =
-                    make_float4(oacc[dt][4 * gq] * inv, oacc[dt][4 * gq + 1] * inv, oacc[dt][4 * gq + 2] * inv,
-                                oacc[dt][4 * gq + 3] * inv);
-        if (h == 0) sl[2 * BS * D + g * BS + 32 * qw + l32] = l > 0.0f ? m * scale + logf(l) : -INFINITY;
-    } else if (i < n && qrow < L) {
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        uint16_t* orow = o + base + (size_t)qrow * D;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                uint16_t vals[4];
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    vals[rr] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(oacc[dt][4 * gq + rr] * inv));
-                uint2 pk;
-                pk.x = (uint32_t)vals[0] | ((uint32_t)vals[1] << 16);
-                pk.y = (uint32_t)vals[2] | ((uint32_t)vals[3] << 16);
-                *reinterpret_cast<uint2*>(orow + 32 * dt + 8 * gq + 4 * h) = pk;
-            }
-        if (lse != nullptr && h == 0)
-            lse[(size_t)bh * L + qrow] = l > 0.0f ? m * scale + logf(l) : -INFINITY;
+    for (int kk = 0; kk < KK; ++kk) {
+        uint4 val = make_uint4(0, 0, 0, 0);
+        if (qrow < L) val = *reinterpret_cast<const uint4*>(q + base + (size_t)qrow * D + 16 * kk + 8 * h);
+        qreg[kk] = __builtin_bit_cast(bf16x8, val);
     }
+    __syncthreads();   // publishes the union list; the scratch is free
+
+    f32x16 oacc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) oacc[dt] = f32x16{};
+    float m = -INFINITY, mb = 0.0f, l = 0.0f;   // running max, m * scale * log2(e), row sum
+
+    // per-lane source offsets of a swizzle period's copies
+    uint32_t cpo[NV];
+#pragma unroll
+    for (int a = 0; a < NV; ++a)
+        cpo[a] = (uint32_t)((lane / LPR) * ROWB + (((lane % LPR) ^ swz<D>(a * RPI + lane / LPR)) << 4));
+    // per-lane LDS offsets of the operands (layouts as in attn_fwd_kernel)
+    const int ka = l32 * ROWB + ((h ^ swz<D>(l32)) << 4);
+    const int s16 = lane & 15, grp = lane >> 4;
+    const int tr_row = 4 * h + (s16 >> 2);
+    const int c0 = 2 * (grp & 1) + ((s16 & 3) >> 1);
+    const int half8 = (s16 & 1) << 3;
+    const int va = tr_row * ROWB + ((c0 ^ swz<D>(tr_row)) << 4) + half8;
+    const int vb = (tr_row + 8) * ROWB + ((c0 ^ swz<D>(tr_row + 8)) << 4) + half8;
+    // (kept in a register: the copies take their LDS address from one)
+    uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)tiles;
+    asm volatile("" : "+s"(lds0));
+    typedef __attribute__((address_space(3))) const uint4 lds_u4_t;
+    // LDS addresses of the operands in the first K and V buffer; the buffer,
+    // unit and row offsets of a read are constants in its offset field, so the
+    // reads need no address arithmetic (the vector unit bounds the kernel)
+    uint32_t kad[KK], vad[2 * DT];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) kad[kk] = lds0 + (uint32_t)(ka ^ (32 * kk));
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        vad[2 * dt] = lds0 + (uint32_t)(2 * TILE + (va ^ (64 * dt)));
+        vad[2 * dt + 1] = lds0 + (uint32_t)(2 * TILE + (vb ^ (64 * dt)));
+    }
+
+    // Copies of wave cw (one swizzle period: 16 rows) of rows r0 .. of block j
+    // of K and of V into LDS offsets kdst / vdst; rows past the sequence's end re-read
+    // its last row.
+    auto copy_rows = [&](int j, int r0, uint32_t kdst, uint32_t vdst, int cw) __attribute__((always_inline)) {
+        const int first = r0 + 16 * cw;
+        const size_t at = ((size_t)j * BS + first) * ROWB;
+        const char* kt = reinterpret_cast<const char*>(k + base) + at;
+        const char* vt = reinterpret_cast<const char*>(v + base) + at;
+        const uint32_t kd = __builtin_amdgcn_readfirstlane(lds0 + kdst + (uint32_t)(16 * cw * ROWB));
+        const uint32_t vd = kd + (vdst - kdst);
+        if (j * BS + BS <= L) {
+#pragma unroll
+            for (int a = 0; a < NV; ++a) {
+                lds_copy16_at(kt + a * 1024, cpo[a], kd + a * 1024);
+                lds_copy16_at(vt + a * 1024, cpo[a], vd + a * 1024);
+            }
+        } else {
+            const int kvalid = L - j * BS;
+#pragma unroll
+            for (int a = 0; a < NV; ++a) {
+                const int row = a * RPI + lane / LPR;
+                const int chunk = (lane % LPR) ^ swz<D>(row);
+                const uint32_t off = (uint32_t)((j * BS + min(first + row, kvalid - 1)) * ROWB + chunk * 16);
+                lds_copy16_at(k + base, off, kd + a * 1024);
+                lds_copy16_at(v + base, off, vd + a * 1024);
+            }
+        }
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // One unit: 32 RT kv rows OFF bytes past the buffers that kad / vad
+    // address, the first `kvalid` of them inside the sequence.
+    auto unit = [&](auto rt_tag, auto off_tag, int kvalid) __attribute__((always_inline)) {
+        constexpr int RT = decltype(rt_tag)::value, OFF = decltype(off_tag)::value;
+        f32x16 sacc[RT];
+        bf16x8 pb[2 * RT];
+        {
+            constexpr int NS = RT * KK, PF = D == 128 ? 4 : 2;   // reads ahead
+            bf16x8 ak[NS];
+            auto load = [&](auto si) __attribute__((always_inline)) {
+                constexpr int s = decltype(si)::value, kk = s / RT, rt = s % RT;
+                ak[s] = __builtin_bit_cast(bf16x8,
+                                           *(lds_u4_t*)(uintptr_t)(kad[kk] + (uint32_t)(OFF + 32 * rt * ROWB)));
+            };
+            static_for<PF>(load);
+            static_for<NS>([&](auto si) __attribute__((always_inline)) {
+                constexpr int s = decltype(si)::value, kk = s / RT, rt = s % RT;
+                if constexpr (s + PF < NS) load(std::integral_constant<int, s + PF>{});
+                sacc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[s], qreg[kk], kk == 0 ? f32x16{} : sacc[rt],
+                                                                   0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        if (kvalid < 32 * RT) {
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const int lim = kvalid - (32 * rt + 4 * h);
+#pragma unroll
+                for (int ii = 0; ii < 16; ++ii)
+                    sacc[rt][ii] = (8 * (ii >> 2) + (ii & 3) >= lim) ? -INFINITY : sacc[rt][ii];
+            }
+        }
+        // the softmax step of attn_fwd_kernel: the running max is kept while
+        // no lane's probabilities of the unit sum past kSumLimit
+        float ps0, ps1;
+        auto exps = [&]() __attribute__((always_inline)) {
+            ps0 = 0.0f;
+            ps1 = 0.0f;
+#pragma unroll
+            for (int qq = 0; qq < RT * 16; ++qq) {
+                const int rt = qq / 16, c1 = (qq / 8) % 2, e = qq % 8;
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[rt][8 * c1 + e], c2, -mb));
+                pb[2 * rt + c1][e] = static_cast<__bf16>(p);
+                if (qq % 2 == 0)
+                    ps0 += p;
+                else
+                    ps1 += p;
+                if (qq % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int c = 0; c < 2 * RT; ++c) asm volatile("" : "+v"(pb[c]));
+        };
+        bool fast = __all(m > -INFINITY);
+        if (fast) {
+            exps();
+            fast = !__any(!(ps0 + ps1 <= kSumLimit));
+        }
+        if (!fast) {
+            asm volatile("" ::: "memory");
+            float mx = -INFINITY;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int ii = 0; ii < 16; ii += 2) mx = fmaxf(mx, fmaxf(sacc[rt][ii], sacc[rt][ii + 1]));
+            mx = max_across_halves(mx);
+            const float m_new = fmaxf(m, mx);
+            const float alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * c2);
+            if (__any(alpha != 1.0f)) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
+                l *= alpha;
+            }
+            m = m_new;
+            mb = m_new == -INFINITY ? 0.0f : m_new * c2;
+            exps();
+        }
+        l += ps0 + ps1;
+        asm volatile("" : "+v"(l), "+v"(m), "+v"(mb));
+        {
+            constexpr int NS = 2 * RT * DT, PF = D == 128 ? 3 : 2;
+            s16x4 va4[NS], vb4[NS];
+            auto load = [&](auto si) __attribute__((always_inline)) {
+                constexpr int s = decltype(si)::value, cc = s / DT, dt = s % DT;
+                va4[s] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds_s16x4_t*)(uintptr_t)(vad[2 * dt] + (uint32_t)(OFF + 16 * cc * ROWB)));
+                vb4[s] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds_s16x4_t*)(uintptr_t)(vad[2 * dt + 1] + (uint32_t)(OFF + 16 * cc * ROWB)));
+            };
+            static_for<PF>(load);
+            static_for<NS>([&](auto si) __attribute__((always_inline)) {
+                constexpr int s = decltype(si)::value, cc = s / DT, dt = s % DT;
+                if constexpr (s + PF < NS) load(std::integral_constant<int, s + PF>{});
+                const s16x8 v8 = {va4[s][0], va4[s][1], va4[s][2], va4[s][3],
+                                  vb4[s][0], vb4[s][1], vb4[s][2], vb4[s][3]};
+                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pb[cc], oacc[dt],
+                                                                   0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    };
+
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qreg[kk]));
+
+    // ---- blocks of both lists: tile t in buffers t & 1, copied one tile ahead by all waves ----
+    const int t0 = min(step0, ns), t1 = min(step1, ns);
+    if (t0 < t1) {
+        int jc = __builtin_amdgcn_readfirstlane(ulist[t0]);
+        int jn = t0 + 1 < t1 ? __builtin_amdgcn_readfirstlane(ulist[t0 + 1]) : 0;
+        copy_rows(jc, 0, 0, 2 * TILE, w);
+        barrier();
+        constexpr int UB = 64 * ROWB;   // bytes per 64-row unit
+        auto tile = [&](int t, auto cur_tag) __attribute__((always_inline)) {
+            constexpr int CUR = decltype(cur_tag)::value, NXT = TILE - CUR;
+            if (t + 1 < t1) copy_rows(jn, 0, NXT, 2 * TILE + NXT, w);
+            const int ja = t + 2 < t1 ? ulist[t + 2] : 0;
+            const int kvalid = L - jc * BS;
+            static_for<BS / 64>([&](auto ui) __attribute__((always_inline)) {
+                constexpr int u = decltype(ui)::value;
+                unit(std::integral_constant<int, 2>{}, std::integral_constant<int, CUR + u * UB>{}, kvalid - 64 * u);
+            });
+            barrier();   // tile t+1 has landed, and every wave is done with tile t's buffers
+            jc = jn;
+            jn = __builtin_amdgcn_readfirstlane(ja);
+        };
+        for (int t = t0; t < t1; t += 2) {
+            tile(t, std::integral_constant<int, 0>{});
+            if (t + 1 < t1) tile(t + 1, std::integral_constant<int, TILE>{});
+        }
+    }
+
+    // ---- blocks of one list only: each group its own, half tiles in two buffers of its own ----
+    const int ce = max(na, nb);
+    const int x0 = min(ce, max(0, step0 - ns)), x1 = min(ce, max(0, step1 - ns));
+    if (x0 < x1) {
+        constexpr int HR = BS / 2, HB = HR * ROWB;
+        const int end = min(g == 0 ? na : nb, x1);   // this group's end of the walk
+        const uint16_t* el = ulist + (g == 0 ? ns : ns + na);
+        const uint32_t kbuf = (uint32_t)(g * TILE), vbuf = (uint32_t)((2 + g) * TILE);
+        if (g == 1) {   // its operands from its own buffers
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kad[kk] += TILE;
+#pragma unroll
+            for (int c = 0; c < 2 * DT; ++c) vad[c] += TILE;
+        }
+        int jc = x0 < end ? __builtin_amdgcn_readfirstlane(el[x0]) : 0;
+        int jn = x0 + 1 < end ? __builtin_amdgcn_readfirstlane(el[x0 + 1]) : 0;
+        if (x0 < end) copy_rows(jc, 0, kbuf, vbuf, qw);
+        barrier();
+        for (int x = x0; x < x1; ++x) {
+            const int ja = x + 2 < end ? el[x + 2] : 0;
+            const int kvalid = L - jc * BS;
+            if (x < end) {
+                copy_rows(jc, HR, kbuf + HB, vbuf + HB, qw);
+                unit(std::integral_constant<int, HR / 32>{}, std::integral_constant<int, 0>{}, kvalid);
+            }
+            barrier();
+            if (x + 1 < end) copy_rows(jn, 0, kbuf, vbuf, qw);
+            if (x < end)
+                unit(std::integral_constant<int, HR / 32>{}, std::integral_constant<int, HB>{}, kvalid - HR);
+            barrier();
+            jc = jn;
+            jn = __builtin_amdgcn_readfirstlane(ja);
+        }
+    }
+
+    l += __shfl_xor(l, 32);
+    if (i < n && qrow < L)
+        store_row<D, BS>(oacc, m, l, scale, slot, g, qw, l32, h, base, bh, qrow, L, o, lse, ws, BH, npairs, S);
     }   // next item
 }
 
@@ -1381,8 +1739,12 @@ hipError_t launch(const uint16_t* q, const uint16_t* k, const uint16_t* v, const
     hipLaunchKernelGGL(plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
     const long items = (long)BH * ((n + 1) / 2) + S;
     const unsigned groups = (unsigned)std::min<long>(slots, items);
-    hipLaunchKernelGGL((attn_fwd_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
-                       q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
+    if constexpr (D * BS == 128 * 128)
+        hipLaunchKernelGGL((attn_fwd_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
+                           q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
+    else
+        hipLaunchKernelGGL((attn_narrow_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
+                           q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
     if (S > 0)
         hipLaunchKernelGGL((merge_kernel<D, BS>), dim3((unsigned)(2 * ncu)), dim3(256), 0, s, ws, BH, n, S, L, o,
                            lse);

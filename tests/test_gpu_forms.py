@@ -61,3 +61,27 @@ def test_attention_more_items_than_resident_groups(d, bs, tail):
         M.mod_block_sparse_attn_fwd(shape, q, k, v, idx, cnt, 0.0, o, lse, ws, ws_bytes)
         assert not torch.isnan(o.float()).any() and not torch.isnan(lse).any()
         _check_rows(host, rows, o, lse, d, bs, L, [(0, 0), (0, 8), (1, 4)], [0, 1, 2, 49, 50, 98, 99, 100])
+
+
+@pytest.mark.parametrize("d,bs,tail", [(128, 64, 1), (64, 128, 65), (64, 128, 64), (64, 64, 33)])
+def test_attention_narrow_tiles_edges(d, bs, tail):
+    """Walks of zero, one and two tiles in either part, and a short tail block
+    in any position of them: its valid rows end inside the first or the
+    second half tile, or exactly between them."""
+    n, H = 9, 3
+    L = (n - 1) * bs + tail
+    host, (q, k, v) = _layer(1, H, L, d, 40 + d + bs + tail, spread=2.5)
+    t = n - 1
+    pick = [[[], [t], [0], [0, t], [t], [t], [1, 2], [1, 2, t], [0, 1, 2, t]],
+            [[0, 1], [2, t], [3], [], [0, 3, t], [0, 3, t], [t], [5], [t]],
+            [[2, 4, t], [2, 4, 6, t], [2], [3], [], [], list(range(n)), [t], [1]]]
+    idx = torch.full((1, H, n, n), -1, dtype=torch.int32)
+    cnt = torch.zeros((1, H, n), dtype=torch.int32)
+    for h in range(H):
+        for i, js in enumerate(pick[h]):
+            cnt[0, h, i] = len(js)
+            idx[0, h, i, :len(js)] = torch.tensor(js, dtype=torch.int32)
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((1, H, L), float("nan"), dtype=torch.float32, device="cuda")
+    M.mod_block_sparse_attn_fwd(M.make_shape(1, H, L, d, bs), q, k, v, idx.cuda(), cnt.cuda(), 0.0, o, lse)
+    _check_rows(host, [pick], o, lse, d, bs, L, [(0, h) for h in range(H)], list(range(n)))
