@@ -478,14 +478,13 @@ mod_status mod_predict_block_mask(mod_stats* s, const void* q, const void* k, in
         const int t2 = s->anchor_step[s->newest], t1 = s->anchor_step[1 - s->newest];
         w = (double)(step - t2) / (double)(t2 - t1);
     }
-    hipError_t e = moddit::launch_extrapolate(X1, X2, w, s->pred, s->BH, n, s->F, hs);
-    if (e != hipSuccess) return hip_fail(e, "extrapolate launch");
+    hipError_t e;
     if (budget->mode == MOD_BUDGET_PATTERN)
-        e = moddit::launch_select_patterns(s->pred, s->gate, s->row_lo, s->row_hi, budget->patterns,
-                                           s->chosen, kv_idx, kv_cnt, s->BH, n, s->nt, s->tb0, hs);
+        e = moddit::launch_select_patterns(X1, X2, w, s->pred, s->gate, s->row_lo, s->row_hi, budget->patterns,
+                                           s->chosen, kv_idx, kv_cnt, s->BH, n, s->F, s->nt, s->tb0, hs);
     else
-        e = moddit::launch_select(s->pred, s->gate, s->row_lo, s->row_hi, budget->mode, topk, tau,
-                                  kv_idx, kv_cnt, s->BH, n, s->nt, s->tb0, hs);
+        e = moddit::launch_select(X1, X2, w, s->pred, s->gate, s->row_lo, s->row_hi, budget->mode, topk, tau,
+                                  kv_idx, kv_cnt, s->BH, n, s->F, s->nt, s->tb0, hs);
     if (e != hipSuccess) return hip_fail(e, "select launch");
     s->has_step = true;
     s->last_step = step;

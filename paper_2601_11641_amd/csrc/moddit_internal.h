@@ -37,25 +37,23 @@ hipError_t launch_solve(const double* r, const int* reg, const double* Sinv, dou
 hipError_t launch_gate(const double* Xa, const double* Xb, int32_t* gate, int BH, int n,
                        int F, double tau_e, hipStream_t s);
 
-// a4: pred [BH, 3n-1] = x2 + (x2 - x1) * w over the c and d parts.
-hipError_t launch_extrapolate(const double* X1, const double* X2, double w, double* pred,
-                              int BH, int n, int F, hipStream_t s);
+// a4 + a5: pred [BH, 3n-1] = x2 + (x2 - x1) * w over the c and d parts of the
+// anchors X1, X2 [BH, 3n-1+F], and per-row selection into compacted lists.
+// row_lo/row_hi: union of the frame regions holding block i; mode 0 = TOPK
+// (k), 1 = MASS (tau).  n: video blocks; ldn >= n: blocks of the whole
+// sequence (lists [BH, ldn, ldn]); tb0: first text block (ldn when there is
+// no text).  The text blocks are kept in every row and the text rows keep
+// every block.
+hipError_t launch_select(const double* X1, const double* X2, double w, double* pred, const int32_t* gate,
+                         const int* row_lo, const int* row_hi, int mode, int k, double tau, int32_t* kv_idx,
+                         int32_t* kv_cnt, int BH, int n, int F, int ldn, int tb0, hipStream_t s);
 
-// a5: per-row selection into compacted lists.  row_lo/row_hi: union of the
-// frame regions holding block i; mode 0 = TOPK (k), 1 = MASS (tau).
-// n: video blocks; ldn >= n: blocks of the whole sequence (lists
-// [BH, ldn, ldn]); tb0: first text block (ldn when there is no text).  The
-// text blocks are kept in every row and the text rows keep every block.
-hipError_t launch_select(const double* pred, const int32_t* gate, const int* row_lo,
-                         const int* row_hi, int mode, int k, double tau, int32_t* kv_idx,
-                         int32_t* kv_cnt, int BH, int n, int ldn, int tb0, hipStream_t s);
-
-// a5, pattern form: the K largest pattern intensities per head (chosen
+// a4 + a5, pattern form: the K largest pattern intensities per head (chosen
 // [BH, 3n-1] bytes, scratch), then per-row lists of the blocks a chosen
 // diagonal or column covers, plus the forced blocks.
-hipError_t launch_select_patterns(const double* pred, const int32_t* gate, const int* row_lo,
-                                  const int* row_hi, int K, uint8_t* chosen, int32_t* kv_idx,
-                                  int32_t* kv_cnt, int BH, int n, int ldn, int tb0, hipStream_t s);
+hipError_t launch_select_patterns(const double* X1, const double* X2, double w, double* pred, const int32_t* gate,
+                                  const int* row_lo, const int* row_hi, int K, uint8_t* chosen, int32_t* kv_idx,
+                                  int32_t* kv_cnt, int BH, int n, int F, int ldn, int tb0, hipStream_t s);
 
 // a6: block-sparse attention forward.  ws: device workspace of ws_bytes
 // bytes, at least attn_plan_bytes(BH, n, 0) (the work plan, rewritten every

@@ -13,7 +13,9 @@
 // block-diagonal support of Section 5.3.
 #include "moddit_internal.h"
 
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace moddit {
 namespace {
@@ -519,36 +521,48 @@ __global__ void gate_kernel(const double* __restrict__ Xa, const double* __restr
 }
 
 // ---------------------------------------------------------------------------
-// a4: linear extrapolation of c and d (Section 5.2).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void extrapolate_kernel(const double* __restrict__ X1,
-                                                               const double* __restrict__ X2,
-                                                               double w,
-                                                               double* __restrict__ pred,
-                                                               int n, int F) {
-    const int bh = blockIdx.y;
-    const int a = blockIdx.x * kThreads + threadIdx.x;
-    const int m = 3 * n - 1, p = 3 * n - 1 + F;
-    if (a >= m) return;
-    const double x2 = X2[(size_t)bh * p + a], x1 = X1[(size_t)bh * p + a];
-    pred[(size_t)bh * m + a] = x2 + (x2 - x1) * w;
-}
-
-// ---------------------------------------------------------------------------
-// a5: per-row selection.  One wave per (head, query block i) up to n = 1024
-// (select_wave_kernel), one work-group of 256 threads per row above
-// (select_kernel), both by the same threshold search.
+// a4 + a5: extrapolation and per-row selection in one launch.
+//
+// A work-group of four waves serves 4 rpw consecutive query rows of one head.
+// It extrapolates the diagonals and columns these rows meet into LDS
+// (X2 + (X2 - X1) w, Section 5.2; n + 4 rpw - 1 and n values), writes its
+// share of the prediction, and each wave then selects rpw rows.
+//
 //   sigma_j = n (c~[j-i] + d~[j]) in fp64, rounded to float: the ranking key.
 //   The non-forced blocks are ranked by (sigma desc, j asc).  TOPK keeps the
 //   first max(0, k - |forced|) of them; MASS keeps the shortest prefix whose
 //   positive key mass, added to the forced blocks' mass, reaches tau of the
 //   row total (fp64 sums; at least one block).  The kept set is compacted in
 //   ascending j.
+// Every free block j holds the order bits of its key (vb, 0 for forced blocks
+// and padding; block lane + 64 e in element e).  The kept free blocks are
+// those whose bits exceed a boundary p, plus the first r in ascending j of
+// those whose bits equal p.  Both budgets ask for the largest threshold at or
+// above which the keys' count (TOPK) or mass (MASS, summed in one fixed order)
+// still reaches the target; that predicate only changes at keys, so any search
+// finds the same set.  A step costs EW compares with a scalar count each
+// (MASS: also EW fp64 additions), so few steps are what counts: the search
+// starts at the boundary of the row before (neighbouring rows shift the
+// diagonals by one), gallops until it has the boundary between two
+// thresholds, halves their distance in order bits, and ends once one key lies
+// between them: 10-12 steps for a first row, 4-6 for the next ones (32 when
+// built bit by bit; interpolating between the counts takes as many).  The
+// ballots that count also place the kept blocks, so the stores of a wave are
+// contiguous.  With the extrapolation: TOPK, 40 heads of 591 blocks 83 -> 44
+// us; MASS, 24 heads of 929 blocks 147 -> 85 us; bound by vector issue.
+//
 // With a text segment after the video (token-type-aware masking) n counts
 // the video blocks, the lists have ldn >= n entries per row, the block tb0
 // shared by the video and the text (tb0 < n) is forced, and every row keeps
-// the text blocks n .. ldn-1 after its video selection.  tb0 >= ldn: none.
+// the text blocks n .. ldn-1 after its video selection; the rows of the text
+// blocks (tb0 .. ldn-1, the last work-groups) keep every block.  tb0 >= ldn:
+// none.
 // ---------------------------------------------------------------------------
+__device__ inline double extrapolated(const double* X1, const double* X2, double w, size_t a) {
+    const double x2 = X2[a], x1 = X1[a];
+    return x2 + (x2 - x1) * w;
+}
+
 __device__ inline uint32_t order_bits(float f) {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -594,168 +608,6 @@ __device__ inline double wave_total_f64(double v) {
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
-// The same selection with one 256-thread work-group per row (n <= 256 E),
-// E keys per thread (blocks t + 256 e, coalesced), by the threshold search of
-// select_wave_kernel below: each step's count or fp64 sum is taken per wave
-// (scalar counts of 64-lane masks; the fixed-order wave total) and over the
-// four waves in wave order, so every thread holds the same bits.
-template <int E>
-__global__ __launch_bounds__(kThreads) void select_kernel(
-    const double* __restrict__ pred, const int32_t* __restrict__ gate,
-    const int* __restrict__ row_lo, const int* __restrict__ row_hi, int mode, int topk,
-    double tau, int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, int n,
-    int ldn, int tb0) {
-    constexpr int NW = kThreads / 64;
-    static_assert(NW == 4, "the wave totals are added as (w0 + w1) + (w2 + w3)");
-    extern __shared__ __align__(16) unsigned char smem[];
-    int* flag = reinterpret_cast<int*>(smem);                     // npad
-    __shared__ double wsum_d[NW];
-    __shared__ int wsum_i[NW];
-
-    const int row = blockIdx.x;
-    const int bh = row / n, i = row % n;
-    const double* c = pred + (size_t)bh * (3 * n - 1);
-    const double* d = c + (2 * n - 1);
-    const bool g = gate[bh] != 0;
-    const int flo = row_lo[i], fhi = row_hi[i];
-    // forced: the frame blocks of i (gate on) and the block shared by the
-    // video and the text segment (tb0 < n), which is a text block
-    const bool tb_in_frames = g && tb0 >= flo && tb0 <= fhi;
-    const int nf = (g ? (fhi - flo + 1) : 0) + ((tb0 < n && !tb_in_frames) ? 1 : 0);
-    const int n_free = n - nf;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-
-    double forced_mass = 0.0;
-    uint32_t vb[E];
-    double ms[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int j = t + kThreads * e;   // coalesced
-        vb[e] = 0;
-        ms[e] = 0.0;
-        int fl = 0;
-        if (j < n) {
-            const double sv = static_cast<double>(n) * (c[j - i + n - 1] + d[j]);
-            const float kf = static_cast<float>(sv);
-            if ((g && j >= flo && j <= fhi) || j == tb0) {
-                fl = 1;
-                forced_mass += fmax(static_cast<double>(kf), 0.0);
-            } else {
-                vb[e] = order_bits(kf);
-                ms[e] = fmax(static_cast<double>(kf), 0.0);
-            }
-        }
-        flag[j] = fl;
-    }
-    auto total_f64 = [&](double v) {    // over the work-group, fixed order
-        v = wave_total_f64(v);
-        if (lane == 0) wsum_d[w] = v;
-        __syncthreads();
-        const double tot = (wsum_d[0] + wsum_d[1]) + (wsum_d[2] + wsum_d[3]);
-        __syncthreads();
-        return tot;
-    };
-    auto count_ge = [&](uint32_t th) {  // free keys with bits >= th (th >= 1)
-        int cnt = 0;
-#pragma unroll
-        for (int e = 0; e < E; ++e) cnt += __popcll(__ballot(vb[e] >= th));
-        if (lane == 0) wsum_i[w] = cnt;
-        __syncthreads();
-        const int tot = (wsum_i[0] + wsum_i[1]) + (wsum_i[2] + wsum_i[3]);
-        __syncthreads();
-        return tot;
-    };
-    auto mass_ge = [&](uint32_t th) {   // their mass (th >= 1)
-        double sm = 0.0;
-#pragma unroll
-        for (int e = 0; e < E; ++e) sm += vb[e] >= th ? ms[e] : 0.0;
-        return total_f64(sm);
-    };
-
-    uint32_t p;     // boundary bits
-    int r;          // keys kept at the boundary, in ascending j
-    int keep = -1;  // free keys kept, when found by count
-    if (mode == 0) {
-        keep = min(n_free, max(0, topk - nf));
-    } else {
-        const double fm = total_f64(forced_mass);
-        const double total = fm + (n_free > 0 ? mass_ge(1u) : 0.0);
-        const double target = tau * total;
-        const int kmin = nf > 0 ? 0 : 1;
-        if (fm >= target) {
-            keep = min(n_free, kmin);
-        } else if (total < target) {
-            keep = n_free;
-        } else {
-            p = 0x80000000u;   // the boundary key has a positive mass
-            for (int b = 30; b >= 0; --b) {
-                const uint32_t th = p | (1u << b);
-                if (fm + mass_ge(th) >= target) p = th;
-            }
-            const double hi = fm + (p < 0xFFFFFFFFu ? mass_ge(p + 1) : 0.0);
-            const int ties = count_ge(p) - (p < 0xFFFFFFFFu ? count_ge(p + 1) : 0);
-            const double mp = fmax(static_cast<double>(order_bits_to_float(p)), 0.0);
-            r = 1;
-            while (r < ties && hi + static_cast<double>(r) * mp < target) ++r;
-        }
-    }
-    if (keep >= 0) {
-        if (keep == 0) {
-            p = 0xFFFFFFFFu;
-            r = 0;
-        } else if (keep >= n_free) {
-            p = 0;
-            r = 0;
-        } else {
-            p = 0;
-            for (int b = 31; b >= 0; --b) {
-                const uint32_t th = p | (1u << b);
-                if (count_ge(th) >= keep) p = th;
-            }
-            r = keep - (p < 0xFFFFFFFFu ? count_ge(p + 1) : 0);
-        }
-    }
-    // flags: 1 kept, 2 at the boundary (resolved below in ascending j)
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int j = t + kThreads * e;
-        if (vb[e] > p)
-            flag[j] = 1;
-        else if (vb[e] == p && vb[e] != 0)
-            flag[j] = 2;
-    }
-    __syncthreads();
-    int f[E];
-    int nt = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        f[e] = flag[t * E + e];
-        nt += f[e] == 2;
-    }
-    int ntie;
-    int tr = block_exclusive_scan(nt, wsum_i, &ntie);   // boundary keys before this thread
-    int cnt = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        if (f[e] == 2) f[e] = tr++ < r ? 1 : 0;
-        cnt += f[e];
-    }
-
-    // compaction in ascending j
-    int total;
-    int pos = block_exclusive_scan(cnt, wsum_i, &total);
-    const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
-    int32_t* out = kv_idx + orow * ldn;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int j = t * E + e;
-        if (f[e]) out[pos++] = j;
-    }
-    // text blocks after the video blocks: kept in every row
-    for (int j = n + t; j < ldn; j += kThreads) out[total + (j - n)] = j;
-    if (t == 0) kv_cnt[orow] = total + (ldn - n);
-}
-
 template <class T>
 __device__ inline T wave_inclusive_scan(T v, int lane) {
 #pragma unroll
@@ -766,288 +618,357 @@ __device__ inline T wave_inclusive_scan(T v, int lane) {
     return v;
 }
 
-__device__ inline void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+// Lanes below this one in a 64-lane mask.
+__device__ inline int mask_rank(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// One wave per row (n <= 64 EW).  Every free block j holds its ranking key
-// as the order bits of sigma_j (vb, 0 for forced blocks and padding) and its
-// positive mass.  The kept free blocks are those whose bits exceed a
-// boundary p, plus the first r in ascending j of those whose bits equal p:
-// the same set as the first keep entries of the (sigma desc, j asc) order.
-//   TOPK: p is the largest 32-bit value with at least keep free keys at or
-//     above it (built bit by bit from the top, 32 wave-wide counts).
-//   MASS: p is the largest value whose keys at or above it, added to the
-//     forced mass, reach tau of the row total (31 fixed-order fp64 wave
-//     sums below the sign bit, which a key of positive mass has set); every
-//     key above p is needed, and r is the fewest keys at p
-//     (all of mass max(sigma_p, 0)) that reach the target with them.
-template <int EW>
-__global__ __launch_bounds__(kThreads) void select_wave_kernel(
-    const double* __restrict__ pred, const int32_t* __restrict__ gate,
-    const int* __restrict__ row_lo, const int* __restrict__ row_hi, int mode, int topk,
-    double tau, int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, int n,
-    int ldn, int tb0, int rows) {
-    constexpr int npad = 64 * EW;
-    constexpr int WPG = kThreads / 64;
-    __shared__ uint8_t flags[WPG][npad];
+// A row of a text block: every block kept.
+__device__ inline void keep_all(int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, size_t orow, int ldn) {
+    int32_t* out = kv_idx + orow * ldn;
+    for (int j = threadIdx.x; j < ldn; j += kThreads) out[j] = j;
+    if (threadIdx.x == 0) kv_cnt[orow] = ldn;
+}
+
+constexpr int kWavesPerGroup = kThreads / 64;
+constexpr int kMaxRowsPerWave = 2;
+
+// The rows of a selection launch: work-groups 0 .. chunks-1 of a head take
+// 4 rpw video rows each, the others one text row.
+struct RowGrid {
+    int rpw, chunks;
+    unsigned groups;
+};
+
+RowGrid row_grid(int BH, int n, int ldn, int tb0) {
+    // One row per wave until that fills the chip's 1024 SIMDs eight deep;
+    // beyond, two, the second starting from the first one's boundary (23,640
+    // TOPK rows: 52 us with one, 44 with two, 44 with four, 54 with eight;
+    // 22,296 MASS rows in the whole prediction: 681, 658, 665 and 701 us).
+    const long rows = (long)BH * n;
+    const int rpw = (int)std::max<long>(1, std::min<long>(kMaxRowsPerWave, rows / 4096));
+    const int chunks = (n + kWavesPerGroup * rpw - 1) / (kWavesPerGroup * rpw);
+    return RowGrid{rpw, chunks, (unsigned)(chunks + std::max(0, ldn - tb0))};
+}
+
+template <int EW, bool MASS>
+__global__ __launch_bounds__(kThreads) void select_rows_kernel(
+    const double* __restrict__ X1, const double* __restrict__ X2, double w, double* __restrict__ pred,
+    const int32_t* __restrict__ gate, const int* __restrict__ row_lo, const int* __restrict__ row_hi, int topk,
+    double tau, int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, int n, int F, int ldn, int tb0,
+    int rpw, int chunks) {
+    __shared__ double cs[64 * EW + kWavesPerGroup * kMaxRowsPerWave];   // diagonals c0 ..
+    __shared__ double ds[64 * EW];                                      // columns
+    const int bh = blockIdx.y;
+    if ((int)blockIdx.x >= chunks) {
+        keep_all(kv_idx, kv_cnt, (size_t)bh * ldn + tb0 + (blockIdx.x - chunks), ldn);
+        return;
+    }
+    const int m = 3 * n - 1;
+    const size_t xo = (size_t)bh * (m + F);
+    const int i0 = blockIdx.x * kWavesPerGroup * rpw;
+    const int i1 = min(n, i0 + kWavesPerGroup * rpw);    // rows [i0, i1)
+    const int c0 = n - i1;                               // diagonal index of (i1 - 1, 0)
+    for (int a = threadIdx.x; a < n + (i1 - i0) - 1; a += kThreads) cs[a] = extrapolated(X1, X2, w, xo + c0 + a);
+    for (int a = threadIdx.x; a < n; a += kThreads) ds[a] = extrapolated(X1, X2, w, xo + 2 * n - 1 + a);
+    {
+        const int per = (m + chunks - 1) / chunks, a1 = min(m, ((int)blockIdx.x + 1) * per);
+        for (int a = blockIdx.x * per + threadIdx.x; a < a1; a += kThreads)
+            pred[(size_t)bh * m + a] = extrapolated(X1, X2, w, xo + a);
+    }
+    __syncthreads();
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int row = blockIdx.x * WPG + wv;        // wave-uniform
-    if (row >= rows) return;
-    uint8_t* flag = flags[wv];
-
-    const int bh = row / n, i = row % n;
-    const double* c = pred + (size_t)bh * (3 * n - 1);
-    const double* d = c + (2 * n - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool g = gate[bh] != 0;
-    const int flo = row_lo[i], fhi = row_hi[i];
-    const bool tb_in_frames = g && tb0 >= flo && tb0 <= fhi;
-    const int nf = (g ? (fhi - flo + 1) : 0) + ((tb0 < n && !tb_in_frames) ? 1 : 0);
-    const int n_free = n - nf;
+    uint32_t guess = 0xBF800000u;    // 1.0: the score of every block of a uniform map
+    uint32_t stride = 1u << 23;      // first gallop step: a factor of two
+    for (int rr = 0; rr < rpw; ++rr) {
+        const int i = i0 + wv * rpw + rr;
+        if (i >= min(i1, tb0)) break;
+        const int flo = row_lo[i], fhi = row_hi[i];
+        // forced: the frame blocks of i (gate on) and the block shared by the
+        // video and the text segment (tb0 < n), which is a text block
+        const bool tb_in_frames = g && tb0 >= flo && tb0 <= fhi;
+        const int nf = (g ? (fhi - flo + 1) : 0) + ((tb0 < n && !tb_in_frames) ? 1 : 0);
+        const int n_free = n - nf;
+        int f0 = flo, f1 = g ? fhi - flo + 1 : 0, f2 = tb0 < n ? tb0 : -1;
+        auto is_forced = [&](int j) { return (unsigned)(j - f0) < (unsigned)f1 || j == f2; };
 
-    double forced_mass = 0.0;
-    uint32_t vb[EW];
-    double ms[EW];
+        double forced_mass = 0.0;
+        uint32_t vb[EW];
+        float ms[EW];    // positive mass of a free key
 #pragma unroll
-    for (int e = 0; e < EW; ++e) {
-        const int j = lane + 64 * e;   // coalesced
-        vb[e] = 0;
-        ms[e] = 0.0;
-        uint8_t fl = 0;
-        if (j < n) {
-            const double sv = static_cast<double>(n) * (c[j - i + n - 1] + d[j]);
-            const float kf = static_cast<float>(sv);
-            if ((g && j >= flo && j <= fhi) || j == tb0) {
-                fl = 1;
-                forced_mass += fmax(static_cast<double>(kf), 0.0);
-            } else {
-                vb[e] = order_bits(kf);
-                ms[e] = fmax(static_cast<double>(kf), 0.0);
+        for (int e = 0; e < EW; ++e) {
+            const int j = lane + 64 * e;
+            vb[e] = 0;
+            ms[e] = 0.0f;
+            if (j < n) {
+                const double sv = static_cast<double>(n) * (cs[j + (i1 - 1 - i)] + ds[j]);
+                const float kf = static_cast<float>(sv);
+                if (is_forced(j)) {
+                    if constexpr (MASS) forced_mass += fmax(static_cast<double>(kf), 0.0);
+                } else {
+                    vb[e] = order_bits(kf);
+                    ms[e] = fmaxf(kf, 0.0f);
+                }
             }
         }
-        flag[j] = fl;
-    }
-    auto count_ge = [&](uint32_t th) {   // free keys with bits >= th (th >= 1)
-        int cnt = 0;
+        auto count_ge = [&](uint32_t th) {   // free keys with bits >= th (th >= 1)
+            int cnt = 0;
 #pragma unroll
-        for (int e = 0; e < EW; ++e) cnt += __popcll(__ballot(vb[e] >= th));
-        return cnt;
-    };
-    auto mass_ge = [&](uint32_t th) {    // their mass (th >= 1)
-        double s = 0.0;
+            for (int e = 0; e < EW; ++e) cnt += __popcll(__ballot(vb[e] >= th));
+            return cnt;
+        };
+        auto mass_ge = [&](uint32_t th) {    // their mass (th >= 1)
+            double s = 0.0;
 #pragma unroll
-        for (int e = 0; e < EW; ++e) s += vb[e] >= th ? ms[e] : 0.0;
-        return wave_total_f64(s);
-    };
-    // largest p with count_ge(p) >= kk (kk >= 1, at most n_free)
-    auto kth_bits = [&](int kk) {
-        uint32_t p = 0;
-        for (int b = 31; b >= 0; --b) {
-            const uint32_t th = p | (1u << b);
-            if (count_ge(th) >= kk) p = th;
-        }
-        return p;
-    };
+            for (int e = 0; e < EW; ++e) s += static_cast<double>(vb[e] >= th ? ms[e] : 0.0f);
+            return wave_total_f64(s);
+        };
 
-    uint32_t p;   // boundary bits
-    int r;        // keys kept at the boundary, in ascending j
-    int keep = -1;  // free keys kept when all or none are
-    if (mode == 0) {
-        keep = min(n_free, max(0, topk - nf));
-    } else {
-        const double fm = wave_total_f64(forced_mass);
-        const double total = fm + (n_free > 0 ? mass_ge(1u) : 0.0);
-        const double target = tau * total;
-        const int kmin = nf > 0 ? 0 : 1;
-        if (fm >= target) {
-            keep = min(n_free, kmin);
-        } else if (total < target) {
-            keep = n_free;
+        uint32_t p = 0;      // boundary bits
+        int r = 0;           // keys kept at the boundary, in ascending j
+        int keep = -1;       // free keys kept when all or none are
+        double fm = 0.0, target = 0.0;
+        if constexpr (MASS) {
+            fm = wave_total_f64(forced_mass);
+            const double total = fm + (n_free > 0 ? mass_ge(1u) : 0.0);
+            target = tau * total;
+            if (fm >= target)
+                keep = min(n_free, nf > 0 ? 0 : 1);
+            else if (total < target)
+                keep = n_free;
         } else {
-            // the boundary key has a positive mass, so its sign bit is set
-            // (every non-negative key's mass is the total's free part)
-            p = 0x80000000u;
-            for (int b = 30; b >= 0; --b) {
-                const uint32_t th = p | (1u << b);
-                if (fm + mass_ge(th) >= target) p = th;
-            }
-            const double hi = fm + (p < 0xFFFFFFFFu ? mass_ge(p + 1) : 0.0);
-            const int ties = count_ge(p) - (p < 0xFFFFFFFFu ? count_ge(p + 1) : 0);
-            const double mp = fmax(static_cast<double>(order_bits_to_float(p)), 0.0);
-            r = 1;
-            while (r < ties && hi + static_cast<double>(r) * mp < target) ++r;
+            keep = min(n_free, max(0, topk - nf));
         }
-    }
-    if (keep >= 0) {
         if (keep == 0) {
             p = 0xFFFFFFFFu;
-            r = 0;
         } else if (keep >= n_free) {
             p = 0;
-            r = 0;
         } else {
-            p = kth_bits(keep);
-            r = keep - (p < 0xFFFFFFFFu ? count_ge(p + 1) : 0);
+            // lo reaches the target (with c_lo keys), hi does not (c_hi); a
+            // bound not yet evaluated has the largest count possible.  By
+            // mass the boundary key is positive, so its sign bit is set.
+            const bool by_mass = MASS && keep < 0;
+            uint32_t lo = by_mass ? 0x80000000u : 1u, hi = 0xFFFFFFFFu;
+            int c_lo = n_free, c_hi = 0;
+            bool have_lo = false, have_hi = false;
+            uint32_t delta = stride, th = guess;
+            while (c_lo - c_hi > 1 && hi - lo > 1) {
+                th = min(max(th, lo + 1), hi - 1);
+                const int c = count_ge(th);
+                if (by_mass ? fm + mass_ge(th) >= target : c >= keep) {
+                    lo = th;
+                    c_lo = c;
+                    have_lo = true;
+                    if (!by_mass && c == keep) break;
+                } else {
+                    hi = th;
+                    c_hi = c;
+                    have_hi = true;
+                }
+                if (have_lo && have_hi) {
+                    th = lo + (hi - lo) / 2;
+                } else {
+                    th = have_lo ? lo + min(delta, hi - lo) : hi - min(delta, hi - lo);
+                    delta = min(delta, 1u << 28) * 8;
+                }
+            }
+            guess = lo;
+            stride = 1u << 18;    // the next row's boundary is within a few percent
+            if (hi - lo > 1 || (!by_mass && c_lo == keep)) {
+                p = lo - 1;   // exactly the keys from lo up
+            } else {
+                p = lo;
+                if (by_mass) {
+                    // the fewest of the equal keys at p that reach the target
+                    const double above = fm + mass_ge(p + 1);
+                    const int ties = count_ge(p) - count_ge(p + 1);
+                    const double mp = fmax(static_cast<double>(order_bits_to_float(p)), 0.0);
+                    r = 1;
+                    while (r < ties && above + static_cast<double>(r) * mp < target) ++r;
+                } else {
+                    r = keep - c_hi;
+                }
+            }
         }
-    }
-    // flags: 1 kept, 2 at the boundary (resolved below in ascending j)
-#pragma unroll
-    for (int e = 0; e < EW; ++e) {
-        const int j = lane + 64 * e;
-        if (vb[e] > p)
-            flag[j] = 1;
-        else if (vb[e] == p && vb[e] != 0)
-            flag[j] = 2;
-    }
-    wave_sync_lds();
-    uint8_t f[EW];
-    int nt = 0;
-#pragma unroll
-    for (int e = 0; e < EW; ++e) {
-        f[e] = flag[EW * lane + e];
-        nt += f[e] == 2;
-    }
-    int tr = wave_inclusive_scan(nt, lane) - nt;   // boundary keys before this lane
-    int cnt = 0;
-#pragma unroll
-    for (int e = 0; e < EW; ++e) {
-        if (f[e] == 2) f[e] = tr++ < r ? 1 : 0;
-        cnt += f[e];
-    }
 
-    // compaction in ascending j
-    const int incl_c = wave_inclusive_scan(cnt, lane);
-    int pos = incl_c - cnt;
-    const int total = __shfl(incl_c, 63);
-    const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
-    int32_t* out = kv_idx + orow * ldn;
+        // compaction in ascending j: block lane + 64 e, element by element
+        // (the forced test is evaluated again rather than kept as EW lane masks)
+        asm volatile("" : "+s"(f0), "+s"(f1), "+s"(f2));
+        const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
+        int32_t* out = kv_idx + orow * ldn;
+        int pos = 0, ties = 0;
 #pragma unroll
-    for (int e = 0; e < EW; ++e) {
-        const int j = EW * lane + e;
-        if (f[e]) out[pos++] = j;
+        for (int e = 0; e < EW; ++e) {
+            const int j = lane + 64 * e;
+            bool kept = vb[e] > p || is_forced(j);
+            if (r > 0) {
+                const bool eq = vb[e] == p;
+                const uint64_t me = __ballot(eq);
+                kept = kept || (eq && ties + mask_rank(me) < r);
+                ties += __popcll(me);
+            }
+            const uint64_t mk = __ballot(kept);
+            if (kept) out[pos + mask_rank(mk)] = j;
+            pos += __popcll(mk);
+        }
+        for (int j = n + lane; j < ldn; j += 64) out[pos + (j - n)] = j;
+        if (lane == 0) kv_cnt[orow] = pos + (ldn - n);
     }
-    for (int j = n + lane; j < ldn; j += 64) out[total + (j - n)] = j;
-    if (lane == 0) kv_cnt[orow] = total + (ldn - n);
 }
 
-inline unsigned cdiv(long a, long b) { return static_cast<unsigned>((a + b - 1) / b); }
-
-}  // namespace
-
 // ---------------------------------------------------------------------------
-// a5, pattern form (Section 5.3): per head, the K largest of the 3n - 1
+// a4 + a5, pattern form (Section 5.3): per head, the K largest of the 3n - 1
 // predicted pattern intensities (diagonals delta = -(n-1)..n-1 at index
 // delta + n - 1, then columns j at 2n - 1 + j), keys at float32 precision,
-// ties by pattern index.  The 64-bit key (order_bits(value) << 32 | ~index)
-// is unique, so the K-th largest key is found exactly by an 8-pass radix
-// select over 8-bit digits; a pattern is chosen iff its key reaches it.
+// ties by pattern index.  One work-group of 1024 threads per head, the order
+// bits of its keys in registers (pattern t + 1024 e in element e): it
+// extrapolates, finds the K-th largest key by four 8-bit radix passes (each
+// a histogram in LDS and a suffix scan of the 256 bins by one wave) and, if
+// some but not all of the keys equal to it are chosen, ranks those by index.
 // Then per row, block (i, j) is kept iff its diagonal or its column is
 // chosen or it is forced; the kept blocks are compacted in ascending j.
+// Both are bound by latency and list writes: 24 heads of 929 blocks, K = n/2,
+// 9 + 23 us (58 + 74 us with 64-bit keys read again in each of eight passes,
+// bins scanned by one thread, and 16 consecutive blocks per thread in the
+// rows, whose reads and stores did not coalesce).
 // ---------------------------------------------------------------------------
-__device__ inline uint64_t pattern_key(const double* v, int p) {
-    return (static_cast<uint64_t>(order_bits(static_cast<float>(v[p]))) << 32) |
-           static_cast<uint64_t>(0xFFFFFFFFu - static_cast<uint32_t>(p));
-}
+constexpr int kRankThreads = 1024;
 
-__global__ __launch_bounds__(kThreads) void pattern_rank_kernel(const double* __restrict__ pred,
-                                                                 uint8_t* __restrict__ chosen,
-                                                                 int n, int K) {
+__global__ __launch_bounds__(kRankThreads) void pattern_rank_kernel(
+    const double* __restrict__ X1, const double* __restrict__ X2, double w, double* __restrict__ pred,
+    uint8_t* __restrict__ chosen, int n, int F, int K) {
+    constexpr int EP = (3 * kMaxBlocks + kRankThreads - 1) / kRankThreads;
     __shared__ uint32_t hist[256];
-    __shared__ uint64_t s_prefix;
-    __shared__ int s_need;
+    __shared__ uint32_t s_digit, s_need, s_ties;
+    __shared__ int wcnt[kRankThreads / 64];
     const int P = 3 * n - 1;
-    const int bh = blockIdx.x, t = threadIdx.x;
-    const double* v = pred + (size_t)bh * P;
-    if (t == 0) {
-        s_prefix = 0;
-        s_need = K;
+    const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int used = (P + kRankThreads - 1) / kRankThreads;   // elements in use
+    uint32_t key[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+        const int q = t + kRankThreads * e;
+        key[e] = 0;
+        if (q < P) {
+            const double v = extrapolated(X1, X2, w, (size_t)bh * (P + F) + q);
+            pred[(size_t)bh * P + q] = v;
+            key[e] = order_bits(static_cast<float>(v));
+        }
     }
-    for (int pass = 0; pass < 8; ++pass) {
-        const int shift = 56 - 8 * pass;
-        const uint64_t hi_mask = pass == 0 ? 0ull : (~0ull << (shift + 8));
-        hist[t] = 0;      // kThreads == 256 bins
+    uint32_t prefix = 0, need = (uint32_t)K, ties = 0;
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 24 - 8 * pass;
+        if (t < 256) hist[t] = 0;
         __syncthreads();
-        const uint64_t prefix = s_prefix;
-        for (int q = t; q < P; q += kThreads) {
-            const uint64_t key = pattern_key(v, q);
-            if ((key & hi_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            if (e < used && t + kRankThreads * e < P && (pass == 0 || (key[e] >> (shift + 8)) == prefix))
+                atomicAdd(&hist[(key[e] >> shift) & 255u], 1u);
         }
         __syncthreads();
-        if (t == 0) {
-            int need = s_need;
-            uint32_t cum = 0;
-            for (int dgt = 255; dgt >= 0; --dgt) {
-                if (cum + hist[dgt] >= (uint32_t)need) {
-                    s_prefix = prefix | (static_cast<uint64_t>(dgt) << shift);
-                    s_need = need - (int)cum;
-                    break;
+        if (wv == 0) {
+            // lane l holds bins 255 - 4l .. 252 - 4l: the largest digits first
+            uint32_t b[4], sum = 0;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                b[x] = hist[255 - (4 * lane + x)];
+                sum += b[x];
+            }
+            uint32_t before = wave_inclusive_scan(sum, lane) - sum;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (before < need && before + b[x] >= need) {
+                    s_digit = 255u - (uint32_t)(4 * lane + x);
+                    s_need = need - before;
+                    s_ties = b[x];
                 }
-                cum += hist[dgt];
+                before += b[x];
             }
         }
         __syncthreads();
+        prefix = (prefix << 8) | s_digit;
+        need = s_need;
+        ties = s_ties;
     }
-    const uint64_t kth = s_prefix;    // the K-th largest key (keys are unique)
-    for (int q = t; q < P; q += kThreads) chosen[(size_t)bh * P + q] = pattern_key(v, q) >= kth ? 1 : 0;
+    // prefix: the K-th largest key; `need` of the `ties` keys equal to it are chosen
+    int before = 0;    // equal keys of smaller index
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+        const int q = t + kRankThreads * e;
+        const bool eq = q < P && key[e] == prefix;
+        bool ch = q < P && (key[e] > prefix || eq);
+        if (e < used && need < ties) {
+            const uint64_t me = __ballot(eq);
+            if (lane == 0) wcnt[wv] = __popcll(me);
+            __syncthreads();
+            int mine = before, all = 0;
+            for (int ww = 0; ww < kRankThreads / 64; ++ww) {
+                mine += ww < wv ? wcnt[ww] : 0;
+                all += wcnt[ww];
+            }
+            __syncthreads();
+            if (eq) ch = mine + mask_rank(me) < (int)need;
+            before += all;
+        }
+        if (q < P) chosen[(size_t)bh * P + q] = ch ? 1 : 0;
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void pattern_rows_kernel(
     const uint8_t* __restrict__ chosen, const int32_t* __restrict__ gate,
     const int* __restrict__ row_lo, const int* __restrict__ row_hi, int32_t* __restrict__ kv_idx,
-    int32_t* __restrict__ kv_cnt, int n, int ldn, int tb0) {
-    __shared__ int wtot[kThreads / 64];
-    constexpr int JPT = kMaxBlocks / kThreads;
-    const int row = blockIdx.x;
-    const int bh = row / n, i = row % n;
+    int32_t* __restrict__ kv_cnt, int n, int ldn, int tb0, int rpw, int chunks) {
+    __shared__ uint8_t cs[kMaxBlocks + kWavesPerGroup * kMaxRowsPerWave];   // the rows' diagonals
+    __shared__ uint8_t ds[kMaxBlocks];                                      // columns
+    const int bh = blockIdx.y;
+    if ((int)blockIdx.x >= chunks) {
+        keep_all(kv_idx, kv_cnt, (size_t)bh * ldn + tb0 + (blockIdx.x - chunks), ldn);
+        return;
+    }
     const uint8_t* ch = chosen + (size_t)bh * (3 * n - 1);
-    const bool g = gate[bh] != 0;
-    const int flo = row_lo[i], fhi = row_hi[i];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    bool keep[JPT];
-    int mine = 0;
-#pragma unroll
-    for (int e = 0; e < JPT; ++e) {
-        const int j = t * JPT + e;
-        keep[e] = j < n && (ch[j - i + n - 1] || ch[2 * n - 1 + j] || (g && j >= flo && j <= fhi) ||
-                            j == tb0);
-        mine += keep[e] ? 1 : 0;
-    }
-    int incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(incl, off);
-        if (lane >= off) incl += y;
-    }
-    if (lane == 63) wtot[w] = incl;
+    const int i0 = blockIdx.x * kWavesPerGroup * rpw;
+    const int i1 = min(n, i0 + kWavesPerGroup * rpw);
+    for (int a = threadIdx.x; a < n + (i1 - i0) - 1; a += kThreads) cs[a] = ch[n - i1 + a];
+    for (int a = threadIdx.x; a < n; a += kThreads) ds[a] = ch[2 * n - 1 + a];
     __syncthreads();
-    int pos = incl - mine, total = 0;
-#pragma unroll
-    for (int ww = 0; ww < kThreads / 64; ++ww) {
-        pos += ww < w ? wtot[ww] : 0;
-        total += wtot[ww];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool g = gate[bh] != 0;
+    for (int rr = 0; rr < rpw; ++rr) {
+        const int i = i0 + wv * rpw + rr;
+        if (i >= min(i1, tb0)) break;
+        const int flo = row_lo[i], fhi = row_hi[i];
+        const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
+        int32_t* out = kv_idx + orow * ldn;
+        int pos = 0;
+        for (int j0 = 0; j0 < n; j0 += 64) {
+            const int j = j0 + lane;
+            const bool kept = j < n && (cs[j + (i1 - 1 - i)] || ds[j] || (g && j >= flo && j <= fhi) || j == tb0);
+            const uint64_t mk = __ballot(kept);
+            if (kept) out[pos + mask_rank(mk)] = j;
+            pos += __popcll(mk);
+        }
+        // text blocks after the video blocks: kept in every row
+        for (int j = n + lane; j < ldn; j += 64) out[pos + (j - n)] = j;
+        if (lane == 0) kv_cnt[orow] = pos + (ldn - n);
     }
-    const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
-    int32_t* out = kv_idx + orow * ldn;
-#pragma unroll
-    for (int e = 0; e < JPT; ++e)
-        if (keep[e]) out[pos++] = t * JPT + e;
-    // text blocks after the video blocks: kept in every row
-    for (int j = n + t; j < ldn; j += kThreads) out[total + (j - n)] = j;
-    if (t == 0) kv_cnt[orow] = total + (ldn - n);
 }
 
-// Token-type-aware masking: the rows of the blocks holding text tokens
-// (tb0 .. ldn-1) keep every block.  Grid (ldn - tb0, BH).
-__global__ __launch_bounds__(kThreads) void text_rows_kernel(int32_t* __restrict__ kv_idx,
-                                                             int32_t* __restrict__ kv_cnt, int ldn,
-                                                             int tb0) {
-    const size_t orow = (size_t)blockIdx.y * ldn + tb0 + blockIdx.x;
-    int32_t* out = kv_idx + orow * ldn;
-    for (int j = threadIdx.x; j < ldn; j += kThreads) out[j] = j;
-    if (threadIdx.x == 0) kv_cnt[orow] = ldn;
+// f(integral_constant<int, i>) for i = A .. B-1.
+template <int A, int B, class Fn>
+inline void static_for(Fn&& f) {
+    if constexpr (A < B) {
+        f(std::integral_constant<int, A>{});
+        static_for<A + 1, B>(f);
+    }
 }
+
+inline unsigned cdiv(long a, long b) { return static_cast<unsigned>((a + b - 1) / b); }
+
+}  // namespace
 
 hipError_t launch_pool(const uint16_t* q, const uint16_t* k, double* qbar, double* kbar,
                        int BH, int L, int L_stride, int d, int bs, int n, hipStream_t s) {
@@ -1116,74 +1037,42 @@ hipError_t launch_gate(const double* Xa, const double* Xb, int32_t* gate, int BH
     return hipGetLastError();
 }
 
-hipError_t launch_extrapolate(const double* X1, const double* X2, double w, double* pred,
-                              int BH, int n, int F, hipStream_t s) {
-    hipLaunchKernelGGL(extrapolate_kernel, dim3(cdiv(3 * n - 1, kThreads), BH), dim3(kThreads), 0,
-                       s, X1, X2, w, pred, n, F);
-    return hipGetLastError();
-}
-
-hipError_t launch_text_rows(int32_t* kv_idx, int32_t* kv_cnt, int BH, int ldn, int tb0, hipStream_t s) {
-    if (tb0 >= ldn) return hipSuccess;
-    hipLaunchKernelGGL(text_rows_kernel, dim3((unsigned)(ldn - tb0), (unsigned)BH), dim3(kThreads), 0, s,
-                       kv_idx, kv_cnt, ldn, tb0);
-    return hipGetLastError();
-}
-
-hipError_t launch_select(const double* pred, const int32_t* gate, const int* row_lo,
-                         const int* row_hi, int mode, int k, double tau, int32_t* kv_idx,
-                         int32_t* kv_cnt, int BH, int n, int ldn, int tb0, hipStream_t s) {
-    int npad_w = 64;
-    while (npad_w < n) npad_w <<= 1;
-    if (npad_w <= 1024) {   // one wave per row
-        const int rows = BH * n;
-        auto gow = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(cdiv(rows, kThreads / 64)), dim3(kThreads), 0, s, pred, gate, row_lo,
-                               row_hi, mode, k, tau, kv_idx, kv_cnt, n, ldn, tb0, rows);
-            return hipGetLastError();
-        };
-        hipError_t e;
-        switch (npad_w / 64) {
-            case 1: e = gow(select_wave_kernel<1>); break;
-            case 2: e = gow(select_wave_kernel<2>); break;
-            case 4: e = gow(select_wave_kernel<4>); break;
-            case 8: e = gow(select_wave_kernel<8>); break;
-            default: e = gow(select_wave_kernel<16>); break;
-        }
-        if (e != hipSuccess) return e;
-        return launch_text_rows(kv_idx, kv_cnt, BH, ldn, tb0, s);
-    }
-    int npad = kThreads;
-    while (npad < n) npad <<= 1;
-    const size_t lds = (size_t)npad * sizeof(int);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)BH * n), dim3(kThreads), lds, s, pred, gate, row_lo, row_hi,
-                           mode, k, tau, kv_idx, kv_cnt, n, ldn, tb0);
+hipError_t launch_select(const double* X1, const double* X2, double w, double* pred, const int32_t* gate,
+                         const int* row_lo, const int* row_hi, int mode, int k, double tau, int32_t* kv_idx,
+                         int32_t* kv_cnt, int BH, int n, int F, int ldn, int tb0, hipStream_t s) {
+    const RowGrid rg = row_grid(BH, n, ldn, tb0);
+    auto go = [&](auto ew) {
+        constexpr int EW = decltype(ew)::value;
+        auto kern = mode == 0 ? select_rows_kernel<EW, false> : select_rows_kernel<EW, true>;
+        hipLaunchKernelGGL(kern, dim3(rg.groups, (unsigned)BH), dim3(kThreads), 0, s, X1, X2, w, pred, gate, row_lo,
+                           row_hi, k, tau, kv_idx, kv_cnt, n, F, ldn, tb0, rg.rpw, rg.chunks);
         return hipGetLastError();
     };
-    hipError_t e;
-    switch (npad / kThreads) {
-        case 1: e = go(select_kernel<1>); break;
-        case 2: e = go(select_kernel<2>); break;
-        case 4: e = go(select_kernel<4>); break;
-        case 8: e = go(select_kernel<8>); break;
-        default: e = go(select_kernel<16>); break;
-    }
-    if (e != hipSuccess) return e;
-    return launch_text_rows(kv_idx, kv_cnt, BH, ldn, tb0, s);
+    // the fewest keys per lane that hold a row (a search step costs one
+    // compare per key slot): every width up to 1024 blocks, then every fourth
+    const int ew = (n + 63) / 64;
+    hipError_t e = hipErrorInvalidValue;
+    static_for<1, 17>([&](auto w) {
+        if (ew == decltype(w)::value) e = go(w);
+    });
+    static_for<5, kMaxBlocks / 256 + 1>([&](auto w) {
+        constexpr int EW = 4 * decltype(w)::value;
+        if (ew > 16 && ew <= EW && ew > EW - 4) e = go(std::integral_constant<int, EW>{});
+    });
+    return e;
 }
 
-hipError_t launch_select_patterns(const double* pred, const int32_t* gate, const int* row_lo,
-                                  const int* row_hi, int K, uint8_t* chosen, int32_t* kv_idx,
-                                  int32_t* kv_cnt, int BH, int n, int ldn, int tb0, hipStream_t s) {
-    hipLaunchKernelGGL(pattern_rank_kernel, dim3((unsigned)BH), dim3(kThreads), 0, s, pred, chosen, n, K);
-    hipError_t e = hipGetLastError();
+hipError_t launch_select_patterns(const double* X1, const double* X2, double w, double* pred, const int32_t* gate,
+                                  const int* row_lo, const int* row_hi, int K, uint8_t* chosen, int32_t* kv_idx,
+                                  int32_t* kv_cnt, int BH, int n, int F, int ldn, int tb0, hipStream_t s) {
+    hipLaunchKernelGGL(pattern_rank_kernel, dim3((unsigned)BH), dim3(kRankThreads), 0, s, X1, X2, w, pred, chosen, n,
+                       F, K);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pattern_rows_kernel, dim3((unsigned)BH * n), dim3(kThreads), 0, s, chosen, gate,
-                       row_lo, row_hi, kv_idx, kv_cnt, n, ldn, tb0);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_text_rows(kv_idx, kv_cnt, BH, ldn, tb0, s);
+    const RowGrid rg = row_grid(BH, n, ldn, tb0);
+    hipLaunchKernelGGL(pattern_rows_kernel, dim3(rg.groups, (unsigned)BH), dim3(kThreads), 0, s, chosen, gate, row_lo,
+                       row_hi, kv_idx, kv_cnt, n, ldn, tb0, rg.rpw, rg.chunks);
+    return hipGetLastError();
 }
 
 }  // namespace moddit
