@@ -190,6 +190,7 @@ struct mod_stats {
     double* qbar = nullptr;
     double* kbar = nullptr;
     double* G = nullptr;
+    double* part = nullptr;    // the fit's row-chunk sums
     double* r = nullptr;
     double* bU = nullptr;
     double* u = nullptr;
@@ -217,7 +218,7 @@ namespace {
 
 void free_stats(mod_stats* s) {
     if (!s) return;
-    void* ptrs[] = {s->qbar, s->kbar, s->G,   s->r,      s->bU,     s->u,   s->X[0], s->X[1],
+    void* ptrs[] = {s->qbar, s->kbar, s->G,   s->part,   s->r,      s->bU,     s->u,   s->X[0], s->X[1],
                     s->pred, s->Sinv, s->reg, s->row_lo, s->row_hi, s->gate, s->chosen};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -231,16 +232,12 @@ bool is_anchor_step(const mod_stats* s, int t) {
     return t % dt == 0;
 }
 
-// rhs -> solve of the statistic in G into the next anchor slot
-mod_status fit_stat_into_next_slot(mod_stats* s, int step, hipStream_t st) {
+// the fit of G (block logits, or the statistic itself) into the next anchor slot
+mod_status fit_map_into_next_slot(mod_stats* s, bool logits, int step, hipStream_t st) {
     const int slot = 1 - s->newest;
-    // the solve's partial-product array u ([kSolveSplit, BH, q], q = n - 1 + F)
-    // is free until the solve and holds the rhs row ranges' sums
-    static_assert(moddit::kRhsChunks * 3 <= moddit::kSolveSplit, "rhs ranges must fit the solve's scratch");
-    hipError_t e = moddit::launch_rhs(s->G, s->reg, s->r, s->u, s->BH, s->n, s->F, st);
-    if (e != hipSuccess) return hip_fail(e, "rhs launch");
-    e = moddit::launch_solve(s->r, s->reg, s->Sinv, s->bU, s->u, s->X[slot], s->BH, s->n, s->F, st);
-    if (e != hipSuccess) return hip_fail(e, "solve launch");
+    const hipError_t e = moddit::launch_fit(s->G, logits, s->reg, s->Sinv, s->part, s->r, s->bU, s->u, s->X[slot],
+                                            s->BH, s->Lv, s->shape.block, s->n, s->F, st);
+    if (e != hipSuccess) return hip_fail(e, "fit launch");
     s->newest = slot;
     s->anchor_step[slot] = step;
     s->n_anchors = std::min(2, s->n_anchors + 1);
@@ -248,16 +245,16 @@ mod_status fit_stat_into_next_slot(mod_stats* s, int step, hipStream_t st) {
     return MOD_OK;
 }
 
-// pool -> block mass -> rhs -> solve into the next anchor slot (statistic 0)
+// pool -> block logits -> block mass, rhs, solve into the next anchor slot (statistic 0)
 mod_status fit_into_next_slot(mod_stats* s, const void* q, const void* k, int step,
                               hipStream_t st) {
     const mod_shape& sh = s->shape;
     hipError_t e = moddit::launch_pool(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                                        s->qbar, s->kbar, s->BH, s->Lv, sh.L, sh.d, sh.block, s->n, st);
     if (e != hipSuccess) return hip_fail(e, "pool launch");
-    e = moddit::launch_block_mass(s->qbar, s->kbar, s->G, s->BH, s->Lv, sh.d, sh.block, s->n, s->scale, st);
-    if (e != hipSuccess) return hip_fail(e, "block-mass launch");
-    return fit_stat_into_next_slot(s, step, st);
+    e = moddit::launch_logits(s->qbar, s->kbar, s->G, s->BH, sh.d, s->n, s->scale, st);
+    if (e != hipSuccess) return hip_fail(e, "block logits launch");
+    return fit_map_into_next_slot(s, true, step, st);
 }
 
 mod_status check_step(const mod_stats* s, int step) {
@@ -345,6 +342,7 @@ mod_status mod_stats_create(const mod_shape* shape, const mod_params* params, mo
         {(void**)&s->qbar, BH * n * shape->d * sizeof(double)},
         {(void**)&s->kbar, BH * n * shape->d * sizeof(double)},
         {(void**)&s->G, BH * n * n * sizeof(double)},
+        {(void**)&s->part, moddit::fit_part_doubles(s->BH, n) * sizeof(double)},
         {(void**)&s->r, BH * s->p * sizeof(double)},
         {(void**)&s->bU, BH * s->q * sizeof(double)},
         {(void**)&s->u, (size_t)moddit::kSolveSplit * BH * s->q * sizeof(double)},   // per-chunk partial products
@@ -419,7 +417,7 @@ mod_status mod_update_stats(mod_stats* s, const void* q, const void* k, const fl
                                              (float)std::log((double)s->params.eta), s->G, s->BH, sh.L, sh.d,
                                              sh.block, s->nt, s->n, hs);
     if (e != hipSuccess) return hip_fail(e, "statistic launch");
-    st = fit_stat_into_next_slot(s, step, hs);
+    st = fit_map_into_next_slot(s, false, step, hs);
     if (st != MOD_OK) return st;
     s->has_step = true;
     s->last_step = step;

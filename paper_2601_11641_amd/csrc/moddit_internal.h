@@ -12,26 +12,25 @@ namespace moddit {
 
 constexpr int kMaxBlocks = 4096;     // largest n (selection keeps a row in LDS)
 constexpr int kSolveSplit = 16;     // k-chunks of the Schur-complement product (fixed: deterministic sum)
-constexpr int kRhsChunks = 4;       // row ranges of the right-hand side sums (fixed: deterministic sum)
 
 // a1: block means of Q and K, fp64 [BH, n, d], over the first L tokens of
 // each head (L_stride tokens apart).
 hipError_t launch_pool(const uint16_t* q, const uint16_t* k, double* qbar, double* kbar,
                        int BH, int L, int L_stride, int d, int bs, int n, hipStream_t s);
 
-// a2: pooled block-mass statistic G [BH, n, n] fp64 (row-stochastic).
-hipError_t launch_block_mass(const double* qbar, const double* kbar, double* G, int BH,
-                             int L, int d, int bs, int n, double scale, hipStream_t s);
+// a2 (part 1): block logits [BH, n, n] fp64 into G.
+hipError_t launch_logits(const double* qbar, const double* kbar, double* G, int BH, int d, int n, double scale,
+                         hipStream_t s);
 
-// a3: right-hand side M^T vec(G) [BH, p] and the structured minimum-norm
-// solve into X [BH, p].  reg: [F][2] inclusive block ranges; Sinv: inverse
-// of the Schur complement [q, q], q = n - 1 + F; bU: scratch [BH, q];
-// u: scratch [kSolveSplit, BH, q] (partial products per k-chunk).
-// part: scratch of kRhsChunks * BH * (3n - 1) doubles (the row ranges' sums).
-hipError_t launch_rhs(const double* G, const int* reg, double* r, double* part, int BH, int n, int F,
-                      hipStream_t s);
-hipError_t launch_solve(const double* r, const int* reg, const double* Sinv, double* bU,
-                        double* u, double* X, int BH, int n, int F, hipStream_t s);
+// a2 (part 2) + a3: if `logits`, G holds block logits and becomes the pooled
+// block-mass statistic (row-stochastic; L tokens in blocks of bs); else G is
+// the statistic.  Then its right-hand side M^T vec(G) and the structured
+// minimum-norm solve into X [BH, p].  reg: [F][2] inclusive block ranges;
+// Sinv: inverse of the Schur complement [q, q], q = n - 1 + F.  Scratch: part
+// (fit_part_doubles), r [BH, p], bU [BH, q], u [kSolveSplit, BH, q].
+size_t fit_part_doubles(int BH, int n);
+hipError_t launch_fit(double* G, bool logits, const int* reg, const double* Sinv, double* part, double* r, double* bU,
+                      double* u, double* X, int BH, int L, int bs, int n, int F, hipStream_t s);
 
 // Block-diagonal gate per head from one or two anchors (Xb may equal Xa).
 hipError_t launch_gate(const double* Xa, const double* Xb, int32_t* gate, int BH, int n,

@@ -21,6 +21,18 @@ namespace moddit {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxSumRows = 16;   // rows of a map that one work-group sums at most
+
+// f(integral_constant<int, i>) for i = A .. B-1.
+template <int A, int B, class Fn>
+inline void static_for(Fn&& f) {
+    if constexpr (A < B) {
+        f(std::integral_constant<int, A>{});
+        static_for<A + 1, B>(f);
+    }
+}
+
+inline unsigned cdiv(long a, long b) { return static_cast<unsigned>((a + b - 1) / b); }
 
 __device__ inline double bf16_bits_to_double(uint32_t bits) {
     return static_cast<double>(__uint_as_float(bits << 16));
@@ -39,22 +51,10 @@ __device__ double block_sum(double v, double* red) {
     return r;
 }
 
-__device__ double block_max(double v, double* red) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
-    }
-    double r = red[0];
-    __syncthreads();
-    return r;
-}
-
-// Exclusive scan over the 256 threads of a workgroup in thread order (a
+// Exclusive scan over the NT threads of a workgroup in thread order (a
 // wave scan, then the wave totals added in wave order: a fixed order).
-// wsum: kThreads / 64 entries of LDS scratch; *total receives the sum.
-template <class T>
+// wsum: NT / 64 entries of LDS scratch; *total receives the sum.
+template <class T, int NT>
 __device__ T block_exclusive_scan(T v, T* wsum, T* total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     T incl = v;
@@ -67,7 +67,7 @@ __device__ T block_exclusive_scan(T v, T* wsum, T* total) {
     __syncthreads();
     T base = T(0), all = T(0);
 #pragma unroll
-    for (int ww = 0; ww < kThreads / 64; ++ww) {
+    for (int ww = 0; ww < NT / 64; ++ww) {
         if (ww < w) base += wsum[ww];
         all += wsum[ww];
     }
@@ -80,8 +80,9 @@ __device__ T block_exclusive_scan(T v, T* wsum, T* total) {
 // thread t scans its contiguous segment, the segment totals are scanned in
 // thread order, and each segment adds its offset (a fixed order).  Every
 // thread of the work-group calls it; a is complete on return.
+template <int NT>
 __device__ void block_inclusive_prefix(double* a, int len, double* wsum) {
-    const int seg = (len + kThreads - 1) / kThreads;
+    const int seg = (len + NT - 1) / NT;
     const int b0 = min(len, (int)threadIdx.x * seg), b1 = min(len, b0 + seg);
     double run = 0.0;
     for (int b = b0; b < b1; ++b) {
@@ -89,7 +90,7 @@ __device__ void block_inclusive_prefix(double* a, int len, double* wsum) {
         a[b] = run;
     }
     double total;
-    const double off = block_exclusive_scan<double>(run, wsum, &total);
+    const double off = block_exclusive_scan<double, NT>(run, wsum, &total);
     for (int b = b0; b < b1; ++b) a[b] += off;
     __syncthreads();
 }
@@ -165,34 +166,41 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(const uint16_t* __restri
 
 // ---------------------------------------------------------------------------
 // a2 (part 1): block logits scale * qbar_i . kbar_j with fp64 matrix
-// products (v_mfma_f64_16x16x4_f64): a 128 x 128 tile per work-group, 64 x 64
-// per wave (4 x 4 product tiles of 16 x 16), channels staged through LDS 16
-// at a time.  Operand layout of the product (16 x 4 times 4 x 16): lane l
-// supplies A[l % 16][l / 16] and B[l / 16][l % 16], and holds D[l / 16 + 4 e]
-// [l % 16] in element e of its result.
+// products (v_mfma_f64_16x16x4_f64): a T x T tile per work-group, T/2 x T/2
+// per wave (product tiles of 16 x 16, those past the last block left out),
+// channels staged through LDS 16 at a time.  Operand layout of the product
+// (16 x 4 times 4 x 16): lane l supplies A[l % 16][l / 16] and B[l / 16]
+// [l % 16], and holds D[l / 16 + 4 e][l % 16] in element e of its result.
+// T = 64 keeps five waves per SIMD (one group's stores run beside another's
+// products); T = 32 where that would leave compute units without work.  24
+// heads of 929 blocks, d = 128: 136 us with 128 x 128 tiles (two waves per
+// SIMD, whose stores all came at the same time), 117 us with 64 x 64 (45
+// TFLOP/s; an fp64 matrix product of the library runs at 72).
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int D>
+template <int D, int T>
 __global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restrict__ qbar,
                                                           const double* __restrict__ kbar,
                                                           double* __restrict__ G, int n,
                                                           double scale) {
-    constexpr int T = 128, KC = 16;
+    constexpr int KC = 16, WT = T / 2, NT = WT / 16;
     static_assert(D % KC == 0 && kThreads == 256, "four waves, 16-channel chunks");
     __shared__ double qs[T][KC + 1];
     __shared__ double ks[T][KC + 1];
     const int bh = blockIdx.z, i0 = blockIdx.y * T, j0 = blockIdx.x * T;
     const double* qb = qbar + (size_t)bh * n * D;
     const double* kb = kbar + (size_t)bh * n * D;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int wr = (w >> 1) * 64, wc = (w & 1) * 64;   // the wave's 64 x 64 sub-tile
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = (w >> 1) * WT, wc = (w & 1) * WT;   // the wave's sub-tile
     const int lm = lane & 15, lk = lane >> 4;
-    f64x4 acc[4][4];
+    // product tiles with a row and a column inside the map
+    const int nu = (min(WT, n - i0 - wr) + 15) / 16, nv = (min(WT, n - j0 - wc) + 15) / 16;
+    f64x4 acc[NT][NT];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int v = 0; v < NT; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
     // the next chunk is loaded into registers while this one is multiplied
     constexpr int PT = T * KC / kThreads;   // values of each operand per thread
     double qn[PT], kn[PT];
@@ -216,142 +224,227 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restri
         if (d0 + KC < D) fetch(d0 + KC);
 #pragma unroll
         for (int kk = 0; kk < KC; kk += 4) {
-            double a[4], b[4];
+            double a[NT], b[NT];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < NT; ++u) {
                 a[u] = qs[wr + 16 * u + lm][kk + lk];
                 b[u] = ks[wc + 16 * u + lm][kk + lk];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < NT; ++u) {
+                if (u >= nu) continue;
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
+                for (int v = 0; v < NT; ++v)
+                    if (v < nv) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
+            }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = i0 + wr + 16 * u + lk + 4 * e;
             if (i >= n) continue;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
+            for (int v = 0; v < NT; ++v) {
                 const int j = j0 + wc + 16 * v + lm;
                 if (j < n) G[((size_t)bh * n + i) * n + j] = scale * acc[u][v][e];
             }
         }
 }
 
-// ---------------------------------------------------------------------------
-// a2 (part 2): G(i, j) = |j| exp(l_ij - max_j l) / sum_j |j| exp(...), one
-// workgroup per (head, row), in place.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void mass_softmax_kernel(double* __restrict__ G, int L,
-                                                                int bs, int n) {
-    constexpr int NPT = kMaxBlocks / kThreads;   // row entries per thread at most
-    __shared__ double red[kThreads];
-    double* g = G + (size_t)blockIdx.x * n;
-    // the row is read once into registers (entry j = threadIdx.x + c kThreads)
-    double x[NPT];
-    double m = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < NPT; ++c) {
-        const int j = threadIdx.x + c * kThreads;
-        x[c] = j < n ? g[j] : -INFINITY;
-        m = fmax(m, x[c]);
+// The wave's total and maximum of a per-lane double in a fixed order, the
+// same bits in every lane: within rows of 16 lanes by DPP (lane pairs, quad
+// pairs, then rotations by 4 and 8, after which lane 0 of a row holds its
+// row's result), then the four rows' results read from lanes 0, 16, 32, 48.
+__device__ inline double dpp_f64(double v, int ctrl_id) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    uint32_t lo = static_cast<uint32_t>(u), hi = static_cast<uint32_t>(u >> 32);
+    switch (ctrl_id) {
+        case 0: lo = __builtin_amdgcn_mov_dpp((int)lo, 0xB1, 0xF, 0xF, false);
+                hi = __builtin_amdgcn_mov_dpp((int)hi, 0xB1, 0xF, 0xF, false); break;   // quad_perm 1,0,3,2
+        case 1: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x4E, 0xF, 0xF, false);
+                hi = __builtin_amdgcn_mov_dpp((int)hi, 0x4E, 0xF, 0xF, false); break;   // quad_perm 2,3,0,1
+        case 2: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x124, 0xF, 0xF, false);
+                hi = __builtin_amdgcn_mov_dpp((int)hi, 0x124, 0xF, 0xF, false); break;  // row_ror:4
+        default: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x128, 0xF, 0xF, false);
+                 hi = __builtin_amdgcn_mov_dpp((int)hi, 0x128, 0xF, 0xF, false); break; // row_ror:8
     }
-    m = block_max(m, red);
-    double s = 0.0;
+    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+__device__ inline double readlane_f64(double v, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), l);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), l);
+    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+__device__ inline double wave_total_f64(double v) {
+    v += dpp_f64(v, 0);
+    v += dpp_f64(v, 1);
+    v += dpp_f64(v, 2);
+    v += dpp_f64(v, 3);
+    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+__device__ inline double wave_max_f64(double v) {
+    v = fmax(v, dpp_f64(v, 0));
+    v = fmax(v, dpp_f64(v, 1));
+    v = fmax(v, dpp_f64(v, 2));
+    v = fmax(v, dpp_f64(v, 3));
+    return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
+}
+
+template <class T>
+__device__ inline T wave_inclusive_scan(T v, int lane) {
 #pragma unroll
-    for (int c = 0; c < NPT; ++c) {
-        const int j = threadIdx.x + c * kThreads;
-        if (j < n) {
-            x[c] = static_cast<double>(min(bs, L - j * bs)) * exp(x[c] - m);
-            s += x[c];
+    for (int off = 1; off < 64; off <<= 1) {
+        const T y = __shfl_up(v, off);
+        if (lane >= off) v += y;
+    }
+    return v;
+}
+
+// p / s from s and inv = 1 / s: one correction step, which leaves the
+// quotient as the division rounds it but for rare last bits.
+__device__ inline double quotient(double p, double s, double inv) {
+    const double g = p * inv;
+    return fma(fma(-g, s, p), inv, g);
+}
+
+// ---------------------------------------------------------------------------
+// a2 (part 2) + a3 (sums): a work-group takes R consecutive rows of one
+// head's map.  SOFTMAX: each row of logits becomes
+//   G(i, j) = |j| exp(l_ij - max_j l) / sum_j |j| exp(...)
+// in place; else the map is only read.  Its entries are added into the column
+// sums (thread t owns columns t + 256 e, in registers) and the diagonal sums
+// (in LDS; consecutive rows shift a diagonal's owner by one thread, and the
+// barriers of the row's reductions lie between) of these rows, stored as this
+// chunk's part of the right-hand side r = M^T vec(G).  One pass over the map
+// instead of three (softmax, diagonals, columns); every sum has a fixed order.
+// Bound by the fp64 exponentials and the map's traffic: 24 heads of 929
+// blocks (166 MB) 62 us, against 63 + 73 us for a softmax pass and
+// a pass with one thread per diagonal or column.
+// ---------------------------------------------------------------------------
+template <int EPT, bool SOFTMAX>
+__global__ __launch_bounds__(kThreads) void map_sums_kernel(double* __restrict__ G, double* __restrict__ part,
+                                                            int L, int bs, int n, int R) {
+    constexpr int NW = kThreads / 64;
+    static_assert(NW == 4, "the wave totals are added as (w0 + w1) + (w2 + w3)");
+    __shared__ double dacc[kThreads * EPT + kMaxSumRows];   // diagonal j - i at j - i + i0 + R - 1
+    __shared__ double rmax[2][NW], rsum[2][NW];
+    const int bh = blockIdx.y, ch = blockIdx.x, nch = gridDim.x;
+    const int i0 = ch * R, rows = min(R, n - i0);
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    double* g = G + ((size_t)bh * n + i0) * n;
+    for (int a = t; a < n + R - 1; a += kThreads) dacc[a] = 0.0;
+    double col[EPT], x[EPT], wgt[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int j = t + kThreads * e;
+        col[e] = 0.0;
+        wgt[e] = static_cast<double>(min(bs, L - j * bs));
+        x[e] = j < n ? g[j] : -INFINITY;
+    }
+    for (int r = 0; r < rows; ++r) {
+        double nx[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int j = t + kThreads * e;
+            nx[e] = (r + 1 < rows && j < n) ? g[(size_t)(r + 1) * n + j] : -INFINITY;
+        }
+        if constexpr (SOFTMAX) {
+            double m = x[0];
+#pragma unroll
+            for (int e = 1; e < EPT; ++e) m = fmax(m, x[e]);
+            m = wave_max_f64(m);
+            if (lane == 0) rmax[r & 1][w] = m;
+            __syncthreads();
+            m = fmax(fmax(rmax[r & 1][0], rmax[r & 1][1]), fmax(rmax[r & 1][2], rmax[r & 1][3]));
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                if (t + kThreads * e < n) {
+                    x[e] = wgt[e] * exp(x[e] - m);
+                    s += x[e];
+                }
+            }
+            s = wave_total_f64(s);
+            if (lane == 0) rsum[r & 1][w] = s;
+            __syncthreads();
+            s = (rsum[r & 1][0] + rsum[r & 1][1]) + (rsum[r & 1][2] + rsum[r & 1][3]);
+            const double inv = 1.0 / s;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                const int j = t + kThreads * e;
+                if (j < n) {
+                    x[e] = quotient(x[e], s, inv);
+                    g[(size_t)r * n + j] = x[e];
+                }
+            }
+        } else {
+            __syncthreads();   // the last row's diagonal sums are complete
+        }
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int j = t + kThreads * e;
+            if (j < n) {
+                col[e] += x[e];
+                dacc[j - r + R - 1] += x[e];
+            }
+            x[e] = nx[e];
         }
     }
-    s = block_sum(s, red);
+    __syncthreads();
+    double* out = part + ((size_t)bh * nch + ch) * (2 * n + R - 1);
+    for (int a = t; a < n + R - 1; a += kThreads) out[a] = dacc[a];
 #pragma unroll
-    for (int c = 0; c < NPT; ++c) {
-        const int j = threadIdx.x + c * kThreads;
-        if (j < n) g[j] = x[c] / s;
+    for (int e = 0; e < EPT; ++e) {
+        const int j = t + kThreads * e;
+        if (j < n) out[n + R - 1 + j] = col[e];
     }
 }
 
-// ---------------------------------------------------------------------------
-// a3 (rhs): r = M^T vec(G): diagonal sums (2n-1), column sums (n) and frame
-// square sums (F).  Diagonals and columns: the rows split into kRhsChunks
-// fixed ranges; per (output, range) one thread takes the range's entries in
-// row order into four interleaved partial sums (rows i mod 4) combined as
-// (s0 + s1) + (s2 + s3), consecutive threads reading consecutive addresses;
-// the ranges' sums are then added in range order.  Frame squares: one
-// work-group per (frame, head), a fixed assignment of entries to threads and
-// a fixed-order tree.  Every sum has a fixed order, so the result is
-// deterministic.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void rhs_kernel(const double* __restrict__ G,
-                                                       double* __restrict__ part, int BH, int n) {
-    const int bh = blockIdx.z, ch = blockIdx.y;
-    const int o = blockIdx.x * kThreads + threadIdx.x;
-    if (o >= 3 * n - 1) return;
-    const double* g = G + (size_t)bh * n * n;
-    // rows [ch n / kRhsChunks, (ch + 1) n / kRhsChunks) of the output's entries
-    const int r0 = (int)((long long)ch * n / kRhsChunks), r1 = (int)((long long)(ch + 1) * n / kRhsChunks) - 1;
-    int i0, i1;
-    size_t step, at;
-    if (o < 2 * n - 1) {                 // diagonal j - i = dl
-        const int dl = o - (n - 1);
-        i0 = max(r0, max(0, -dl));
-        i1 = min(r1, min(n - 1, n - 1 - dl));
-        step = (size_t)n + 1;
-        at = (size_t)i0 * n + i0 + dl;
-    } else {                             // column j
-        i0 = r0;
-        i1 = r1;
-        step = (size_t)n;
-        at = (size_t)i0 * n + (o - (2 * n - 1));
-    }
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int i = i0;
-    for (; i + 3 <= i1; i += 4, at += 4 * step) {
-        s0 += g[at];
-        s1 += g[at + step];
-        s2 += g[at + 2 * step];
-        s3 += g[at + 3 * step];
-    }
-    for (int q = 0; i <= i1; ++i, ++q, at += step) {
-        if (q == 0) s0 += g[at];
-        else if (q == 1) s1 += g[at];
-        else s2 += g[at];
-    }
-    part[((size_t)ch * BH + bh) * (3 * n - 1) + o] = (s0 + s1) + (s2 + s3);
-}
-
-// The ranges' sums of every diagonal and column, added in range order.
-__global__ __launch_bounds__(kThreads) void rhs_sum_kernel(const double* __restrict__ part,
-                                                           double* __restrict__ r, int BH, int n, int F) {
-    const int bh = blockIdx.y;
-    const int o = blockIdx.x * kThreads + threadIdx.x;
-    if (o >= 3 * n - 1) return;
-    double s = part[(size_t)bh * (3 * n - 1) + o];
-#pragma unroll
-    for (int ch = 1; ch < kRhsChunks; ++ch) s += part[((size_t)ch * BH + bh) * (3 * n - 1) + o];
-    r[(size_t)bh * (3 * n - 1 + F) + o] = s;
-}
-
-__global__ __launch_bounds__(kThreads) void rhs_frame_kernel(const double* __restrict__ G,
-                                                             const int* __restrict__ reg,
-                                                             double* __restrict__ r, int n, int F) {
+// The chunks' diagonal and column sums added in chunk order, and the sums of
+// the frame squares (one work-group per frame, a fixed assignment of entries
+// to threads and a fixed-order tree).  Grid (ceil((3n - 1) / 256) + F, BH).
+__global__ __launch_bounds__(kThreads) void rhs_kernel(const double* __restrict__ part,
+                                                       const double* __restrict__ G,
+                                                       const int* __restrict__ reg, double* __restrict__ r,
+                                                       int n, int F, int nch, int R) {
     __shared__ double red[kThreads];
-    const int f = blockIdx.x, bh = blockIdx.y;
-    const int lo = reg[2 * f], hi = reg[2 * f + 1], sz = hi - lo + 1;
-    const double* g = G + (size_t)bh * n * n;
+    const int bh = blockIdx.y, nb = gridDim.x - F;
+    double* rr = r + (size_t)bh * (3 * n - 1 + F);
+    if ((int)blockIdx.x >= nb) {
+        const int f = blockIdx.x - nb;
+        const int lo = reg[2 * f], hi = reg[2 * f + 1], sz = hi - lo + 1;
+        const double* g = G + (size_t)bh * n * n;
+        double s = 0.0;
+        for (int e = threadIdx.x; e < sz * sz; e += kThreads) s += g[(size_t)(lo + e / sz) * n + lo + e % sz];
+        s = block_sum(s, red);
+        if (threadIdx.x == 0) rr[3 * n - 1 + f] = s;
+        return;
+    }
+    const int o = blockIdx.x * kThreads + threadIdx.x;
+    if (o >= 3 * n - 1) return;
+    const int stride = 2 * n + R - 1;
+    const double* pp = part + (size_t)bh * nch * stride;
+    int ca = 0, cb = nch - 1, at = n + R - 1 + (o - (2 * n - 1)), step = stride;   // a column
+    if (o < 2 * n - 1) {
+        // diagonal dl lies in chunk c at dl + c R + R - 1, if
+        // that is in [0, n + R - 2]
+        const int dl = o - (n - 1);
+        ca = max(0, -dl / R);
+        cb = min(nch - 1, (n - 1 - dl) / R);
+        at = dl + R - 1;
+        step = stride + R;
+    }
     double s = 0.0;
-    for (int e = threadIdx.x; e < sz * sz; e += kThreads) s += g[(size_t)(lo + e / sz) * n + lo + e % sz];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) r[(size_t)bh * (3 * n - 1 + F) + 3 * n - 1 + f] = s;
+#pragma unroll 8
+    for (int c = ca; c <= cb; ++c) s += pp[(ptrdiff_t)c * step + at];
+    rr[o] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -390,92 +483,110 @@ __global__ __launch_bounds__(kThreads) void solve_pre_kernel(const double* __res
     __syncthreads();
     // column rows of W^T: the n diagonals column j crosses, y[j .. j + n - 1],
     // as a difference of the prefix sums
-    block_inclusive_prefix(y, 2 * n - 1, wsum);
+    block_inclusive_prefix<kThreads>(y, 2 * n - 1, wsum);
     if (j < n - 1) s = y[j + n - 1] - (j > 0 ? y[j - 1] : 0.0);
     if (j < q) bU[(size_t)bh * q + j] = (j < n - 1 ? rr[2 * n - 1 + j] : rr[3 * n - 1 + (j - (n - 1))]) - s;
 }
 
 // u[h] = S^{-1} bU[h] for all heads, split over kSolveSplit fixed chunks of
-// k: part[c][h][j] = sum over k in chunk c (ascending) of S^{-1}[k][j] bU[h][k]
-// (S^{-1} symmetric, read row-wise: a wave's lanes read 64 consecutive
-// columns).  The post kernel adds the chunks in order, so the result does
-// not depend on the launch.  Grid: (column chunks of 64, kSolveSplit); wave
-// w takes heads w*8.. in passes of 32.
+// k and the four waves of a work-group: part[c][h][j] = sum over k in chunk c
+// of S^{-1}[k][j] bU[h][k] (S^{-1} symmetric, read row-wise: a wave's lanes
+// read 64 consecutive columns; each wave a quarter of the chunk, ascending,
+// the quarters added in order).  The post kernel adds the chunks in order, so
+// the result does not depend on the launch.  Grid: (column chunks of 64,
+// kSolveSplit).  Bound by the latency of S^{-1} (7 MB at n = 929, shared by
+// every head), so a wave loads 16 rows at once and reuses them for 8 heads.
 __global__ __launch_bounds__(kThreads) void solve_gemv_kernel(const double* __restrict__ Sinv,
                                                               const double* __restrict__ bU,
                                                               double* __restrict__ part, int q,
                                                               int BH) {
-    constexpr int HW = 8;
-    // a wave's right-hand sides, 64 k at a time: bs[w][k - kb][hh]
-    __shared__ double bs[kThreads / 64][64][HW];
+    constexpr int HW = 8, KB = 16, NW = kThreads / 64;
+    __shared__ double bs[NW][KB][HW];        // a wave's right-hand sides, 16 k at a time
+    __shared__ double red[NW][HW][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = blockIdx.x * 64 + lane;
     const int c = blockIdx.y;
     const int kc = (q + kSolveSplit - 1) / kSolveSplit;
-    const int k0 = min(q, c * kc), k1 = min(q, k0 + kc);
-    for (int h0 = w * HW; h0 < BH; h0 += (kThreads / 64) * HW) {
+    const int k0 = min(q, c * kc), k1 = min(q, k0 + kc), kw = (k1 - k0 + NW - 1) / NW;
+    const int ka = min(k1, k0 + w * kw), kz = min(k1, ka + kw);
+    const double* col = Sinv + min(j, q - 1);
+    for (int h0 = 0; h0 < BH; h0 += HW) {
         double acc[HW];
 #pragma unroll
         for (int hh = 0; hh < HW; ++hh) acc[hh] = 0.0;
-        for (int kb = k0; kb < k1; kb += 64) {
-            const int kn = min(64, k1 - kb);
+        for (int kb = ka; kb < kz; kb += KB) {
+            double a[KB];
+#pragma unroll
+            for (int kk = 0; kk < KB; ++kk) a[kk] = col[(size_t)min(kb + kk, kz - 1) * q];
             // (the wave's LDS operations run in order: the previous pass's
             // reads are done before these writes)
 #pragma unroll
-            for (int hh = 0; hh < HW; ++hh)
-                bs[w][lane][hh] = (lane < kn && h0 + hh < BH) ? bU[(size_t)(h0 + hh) * q + kb + lane] : 0.0;
-            if (j < q) {
-#pragma unroll 4
-                for (int kk = 0; kk < kn; ++kk) {
-                    const double a = Sinv[(size_t)(kb + kk) * q + j];
-#pragma unroll
-                    for (int hh = 0; hh < HW; ++hh) acc[hh] = fma(a, bs[w][kk][hh], acc[hh]);
-                }
+            for (int x = 0; x < KB * HW / 64; ++x) {
+                const int e = lane + 64 * x, hh = e / KB, kk = e % KB;
+                bs[w][kk][hh] = (kb + kk < kz && h0 + hh < BH) ? bU[(size_t)(h0 + hh) * q + kb + kk] : 0.0;
             }
-        }
-        if (j < q) {
 #pragma unroll
-            for (int hh = 0; hh < HW; ++hh)
-                if (h0 + hh < BH) part[((size_t)c * BH + h0 + hh) * q + j] = acc[hh];
+            for (int kk = 0; kk < KB; ++kk)
+#pragma unroll
+                for (int hh = 0; hh < HW; ++hh) acc[hh] = fma(a[kk], bs[w][kk][hh], acc[hh]);
         }
+#pragma unroll
+        for (int hh = 0; hh < HW; ++hh) red[w][hh][lane] = acc[hh];
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < HW / NW; ++x) {
+            const int hh = w + NW * x;
+            if (j < q && h0 + hh < BH)
+                part[((size_t)c * BH + h0 + hh) * q + j] =
+                    ((red[0][hh][lane] + red[1][hh][lane]) + red[2][hh][lane]) + red[3][hh][lane];
+        }
+        __syncthreads();   // red may be rewritten
     }
 }
 
-__global__ __launch_bounds__(kThreads) void solve_post_kernel(const double* __restrict__ r,
-                                                              const double* __restrict__ u,
-                                                              const int* __restrict__ reg,
-                                                              double* __restrict__ X, int n,
-                                                              int F, int BH) {
+// c = Dc^{-1} (r_C - W u), then the minimum-norm gauge: the component of X
+// along z = [1, -1, 0] removed.  One work-group of 1024 threads per head;
+// every entry of X that a thread corrects, it wrote itself.
+constexpr int kPostThreads = 1024;
+
+__global__ __launch_bounds__(kPostThreads) void solve_post_kernel(const double* __restrict__ r,
+                                                                  const double* __restrict__ u,
+                                                                  const int* __restrict__ reg,
+                                                                  double* __restrict__ X, int n,
+                                                                  int F, int BH) {
     extern __shared__ double us[];   // q: u, then the prefix of its first n - 1 entries; then F frame sizes
-    __shared__ double wsum[kThreads / 64];
+    __shared__ double wsum[kPostThreads / 64];
     __shared__ int szmax;
-    const int bh = blockIdx.x;       // one work-group per head
+    const int bh = blockIdx.x, t = threadIdx.x;
     const int p = 3 * n - 1 + F, q = n - 1 + F;
     int* sz = reinterpret_cast<int*>(us + q);
-    if (threadIdx.x == 0) szmax = 0;
+    if (t == 0) szmax = 0;
     __syncthreads();
-    for (int f = threadIdx.x; f < F; f += kThreads) {
+    for (int f = t; f < F; f += kPostThreads) {
         sz[f] = reg[2 * f + 1] - reg[2 * f] + 1;
         atomicMax(&szmax, sz[f]);
     }
     const double* rr = r + (size_t)bh * p;
     double* x = X + (size_t)bh * p;
+    double net = 0.0;   // sum(c) - sum(d) of this thread's entries
     // u = sum of the k-chunk partial products, in chunk order; the d and e
-    // parts of X are u itself
-    for (int a = threadIdx.x; a < q; a += kThreads) {
+    // parts of X are u itself (d_{n-1}, the gauge column dropped, is 0)
+    for (int a = t; a < q; a += kPostThreads) {
         double v = 0.0;
+#pragma unroll
         for (int c = 0; c < kSolveSplit; ++c) v += u[((size_t)c * BH + bh) * q + a];
         us[a] = v;
-        if (a < n - 1) x[2 * n - 1 + a] = v;
+        if (a < n - 1) net -= v;
         else x[3 * n - 1 + (a - (n - 1))] = v;
     }
-    if (threadIdx.x == 0) x[3 * n - 2] = 0.0;   // d_{n-1}: the gauge column dropped
     __syncthreads();
-    block_inclusive_prefix(us, n - 1, wsum);
-    // c = Dc^{-1} (r_C - W u): the columns crossing diagonal dl are a window
-    // of d (a difference of the prefix sums), the frames' weights max(0,
-    // |R_f| - |dl|) multiply e
-    for (int a = threadIdx.x; a < 2 * n - 1; a += kThreads) {
+    // the d part, before the prefix takes its place
+    for (int a = t; a < n; a += kPostThreads) x[2 * n - 1 + a] = a < n - 1 ? us[a] : 0.0;
+    __syncthreads();
+    block_inclusive_prefix<kPostThreads>(us, n - 1, wsum);
+    // c: the columns crossing diagonal dl are a window of d (a difference of
+    // the prefix sums), the frames' weights max(0, |R_f| - |dl|) multiply e
+    for (int a = t; a < 2 * n - 1; a += kPostThreads) {
         const int dl = a - (n - 1);
         const int j0 = max(0, dl), j1 = min(n - 2, dl + n - 1);
         double s = j1 >= j0 ? us[j1] - (j0 > 0 ? us[j0 - 1] : 0.0) : 0.0;
@@ -485,21 +596,202 @@ __global__ __launch_bounds__(kThreads) void solve_post_kernel(const double* __re
                 if (w > 0) s += static_cast<double>(w) * us[n - 1 + f];
             }
         }
-        x[a] = (rr[a] - s) / static_cast<double>(n - abs(dl));
+        const double cv = (rr[a] - s) / static_cast<double>(n - abs(dl));
+        x[a] = cv;
+        net += cv;
     }
+    double total;
+    (void)block_exclusive_scan<double, kPostThreads>(net, wsum, &total);
+    const double alpha = total / static_cast<double>(3 * n - 1);
+    for (int a = t; a < 2 * n - 1; a += kPostThreads) x[a] -= alpha;
+    for (int j = t; j < n; j += kPostThreads) x[2 * n - 1 + j] += alpha;
 }
 
-// Minimum-norm gauge: remove the component of X along z = [1, -1, 0].
-__global__ __launch_bounds__(kThreads) void solve_gauge_kernel(double* __restrict__ X, int n, int F) {
-    __shared__ double red[kThreads];
-    const int p = 3 * n - 1 + F;
-    double* x = X + (size_t)blockIdx.x * p;
-    double part = 0.0;   // sum(c) - sum(d) of this thread's entries
-    for (int a = threadIdx.x; a < 2 * n - 1; a += kThreads) part += x[a];
-    for (int j = threadIdx.x; j < n; j += kThreads) part -= x[2 * n - 1 + j];
-    const double alpha = block_sum(part, red) / static_cast<double>(3 * n - 1);
-    for (int a = threadIdx.x; a < 2 * n - 1; a += kThreads) x[a] -= alpha;
-    for (int j = threadIdx.x; j < n; j += kThreads) x[2 * n - 1 + j] += alpha;
+// ---------------------------------------------------------------------------
+// a2 (part 2) + a3 for short maps (n <= NC, F <= NC): one work-group per head
+// holds the map in LDS and goes from the logits (SOFTMAX) or the stored map to
+// X in one launch.  The steps are those of map_sums_kernel, rhs_kernel and the
+// solve kernels.  A fit of so few blocks is a chain of launches and of
+// latencies within them, not work: 8 heads of 64 blocks took 55 us in nine launches, 18 in
+// two (logits and this one).
+// ---------------------------------------------------------------------------
+constexpr int kFitThreads = 1024;
+
+template <int NC, bool SOFTMAX>
+__global__ __launch_bounds__(kFitThreads) void fit_small_kernel(double* __restrict__ G, const int* __restrict__ reg,
+                                                                const double* __restrict__ Sinv,
+                                                                double* __restrict__ X, int L, int bs, int n,
+                                                                int F) {
+    constexpr int NW = kFitThreads / 64, EW = NC / 64;
+    constexpr int SPL = kFitThreads / (4 * NC);     // row ranges of a diagonal's or column's sum
+    constexpr int KSPL = kFitThreads / (2 * NC);    // k ranges of the product with S^{-1}
+    __shared__ double g[NC][NC + 1];
+    __shared__ double rr[4 * NC], y[2 * NC], py[2 * NC], bu[2 * NC], uu[2 * NC], pu[NC];
+    __shared__ double part[kFitThreads];
+    __shared__ double wsum[NW];
+    __shared__ int sz[NC];
+    __shared__ int szmax;
+    const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int m = 3 * n - 1, q = n - 1 + F;
+    double* gg = G + (size_t)bh * n * n;
+    if (t == 0) szmax = 0;
+    // the map: a wave per row
+    for (int i = w; i < n; i += NW) {
+        double x[EW];
+        double mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < EW; ++e) {
+            const int j = lane + 64 * e;
+            x[e] = j < n ? gg[(size_t)i * n + j] : -INFINITY;
+            mx = fmax(mx, x[e]);
+        }
+        if constexpr (SOFTMAX) {
+            mx = wave_max_f64(mx);
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < EW; ++e) {
+                const int j = lane + 64 * e;
+                if (j < n) {
+                    x[e] = static_cast<double>(min(bs, L - j * bs)) * exp(x[e] - mx);
+                    s += x[e];
+                }
+            }
+            s = wave_total_f64(s);
+            const double inv = 1.0 / s;
+#pragma unroll
+            for (int e = 0; e < EW; ++e) {
+                const int j = lane + 64 * e;
+                x[e] = quotient(x[e], s, inv);
+                if (j < n) gg[(size_t)i * n + j] = x[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EW; ++e)
+            if (lane + 64 * e < n) g[i][lane + 64 * e] = x[e];
+    }
+    __syncthreads();
+    // sums: diagonals and columns over SPL row ranges, frame squares by wave
+    for (int f = t; f < F; f += kFitThreads) {
+        sz[f] = reg[2 * f + 1] - reg[2 * f] + 1;
+        atomicMax(&szmax, sz[f]);
+    }
+    {
+        const int o = t % (4 * NC), c = t / (4 * NC);
+        const int r0 = c * n / SPL, r1 = (c + 1) * n / SPL;
+        double s = 0.0;
+        if (o < 2 * n - 1) {
+            const int dl = o - (n - 1);
+            for (int i = max(r0, -dl); i < min(r1, n - dl); ++i) s += g[i][i + dl];
+        } else if (o < m) {
+            for (int i = r0; i < r1; ++i) s += g[i][o - (2 * n - 1)];
+        }
+        part[t] = s;
+    }
+    for (int f = w; f < F; f += NW) {
+        const int lo = reg[2 * f], side = reg[2 * f + 1] - lo + 1;
+        double s = 0.0;
+        for (int e = lane; e < side * side; e += 64) s += g[lo + e / side][lo + e % side];
+        s = wave_total_f64(s);
+        if (lane == 0) rr[m + f] = s;
+    }
+    __syncthreads();
+    if (t < m) {
+        double s = part[t];
+#pragma unroll
+        for (int c = 1; c < SPL; ++c) s += part[c * 4 * NC + t];
+        rr[t] = s;
+        if (t < 2 * n - 1) y[t] = s / static_cast<double>(n - abs(t - (n - 1)));
+    }
+    __syncthreads();
+    // b_U = r_U - W^T y: prefix sums of y for the columns, a wave per frame
+    if (w == NW - 1) {
+        constexpr int S = 2 * NC / 64;
+        double run = 0.0, v[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+            const int a = S * lane + e;
+            run += a < 2 * n - 1 ? y[a] : 0.0;
+            v[e] = run;
+        }
+        const double off = wave_inclusive_scan(run, lane) - run;
+#pragma unroll
+        for (int e = 0; e < S; ++e) py[S * lane + e] = v[e] + off;
+    }
+    for (int f = w; f < F; f += NW) {
+        const int side = sz[f];
+        double s = 0.0;
+        for (int e = lane; e < 2 * side - 1; e += 64) {
+            const int dl = e - (side - 1);
+            s += static_cast<double>(side - abs(dl)) * y[dl + n - 1];
+        }
+        s = wave_total_f64(s);
+        if (lane == 0) bu[n - 1 + f] = rr[m + f] - s;
+    }
+    __syncthreads();
+    if (t < n - 1) bu[t] = rr[2 * n - 1 + t] - (py[t + n - 1] - (t > 0 ? py[t - 1] : 0.0));
+    __syncthreads();
+    // u = S^{-1} b_U over KSPL ranges of k
+    {
+        const int j = t % (2 * NC), c = t / (2 * NC);
+        const int k0 = c * q / KSPL, k1 = (c + 1) * q / KSPL;
+        double s = 0.0;
+        if (j < q) {
+#pragma unroll 8
+            for (int k = k0; k < k1; ++k) s = fma(Sinv[(size_t)k * q + j], bu[k], s);
+        }
+        part[t] = s;
+    }
+    __syncthreads();
+    if (t < q) {
+        double s = part[t];
+#pragma unroll
+        for (int c = 1; c < KSPL; ++c) s += part[c * 2 * NC + t];
+        uu[t] = s;
+    }
+    __syncthreads();
+    if (w == 0) {
+        double run = 0.0, v[EW];
+#pragma unroll
+        for (int e = 0; e < EW; ++e) {
+            const int a = EW * lane + e;
+            run += a < n - 1 ? uu[a] : 0.0;
+            v[e] = run;
+        }
+        const double off = wave_inclusive_scan(run, lane) - run;
+#pragma unroll
+        for (int e = 0; e < EW; ++e) pu[EW * lane + e] = v[e] + off;
+    }
+    __syncthreads();
+    // c = Dc^{-1} (r_C - W u), the gauge, and X
+    double v = 0.0, net = 0.0;
+    if (t < 2 * n - 1) {
+        const int dl = t - (n - 1);
+        const int j0 = max(0, dl), j1 = min(n - 2, dl + n - 1);
+        double s = j1 >= j0 ? pu[j1] - (j0 > 0 ? pu[j0 - 1] : 0.0) : 0.0;
+        if (abs(dl) < szmax) {
+            for (int f = 0; f < F; ++f) {
+                const int side = sz[f] - abs(dl);
+                if (side > 0) s += static_cast<double>(side) * uu[n - 1 + f];
+            }
+        }
+        v = (rr[t] - s) / static_cast<double>(n - abs(dl));
+        net = v;
+    } else if (t < m) {
+        const int j = t - (2 * n - 1);
+        v = j < n - 1 ? uu[j] : 0.0;   // d_{n-1}: the gauge column dropped
+        net = -v;
+    }
+    net = wave_total_f64(net);
+    if (lane == 0) wsum[w] = net;
+    __syncthreads();
+    double total = 0.0;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) total += wsum[ww];
+    const double alpha = total / static_cast<double>(m);
+    double* x = X + (size_t)bh * (m + F);
+    if (t < m) x[t] = t < 2 * n - 1 ? v - alpha : v + alpha;
+    else if (t < m + F) x[t] = uu[n - 1 + (t - m)];
 }
 
 // ---------------------------------------------------------------------------
@@ -571,51 +863,6 @@ __device__ inline uint32_t order_bits(float f) {
 __device__ inline float order_bits_to_float(uint32_t k) {
     const uint32_t u = (k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k;
     return __uint_as_float(u);
-}
-
-// The wave's total of a per-lane double in a fixed order, the same bits in
-// every lane: sums within rows of 16 lanes by DPP (lane pairs, quad pairs,
-// then rotations by 4 and 8, after which lane 0 of a row holds its row's
-// sum), then the four row sums read from lanes 0, 16, 32 and 48.
-__device__ inline double dpp_f64(double v, int ctrl_id) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    uint32_t lo = static_cast<uint32_t>(u), hi = static_cast<uint32_t>(u >> 32);
-    switch (ctrl_id) {
-        case 0: lo = __builtin_amdgcn_mov_dpp((int)lo, 0xB1, 0xF, 0xF, false);
-                hi = __builtin_amdgcn_mov_dpp((int)hi, 0xB1, 0xF, 0xF, false); break;   // quad_perm 1,0,3,2
-        case 1: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x4E, 0xF, 0xF, false);
-                hi = __builtin_amdgcn_mov_dpp((int)hi, 0x4E, 0xF, 0xF, false); break;   // quad_perm 2,3,0,1
-        case 2: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x124, 0xF, 0xF, false);
-                hi = __builtin_amdgcn_mov_dpp((int)hi, 0x124, 0xF, 0xF, false); break;  // row_ror:4
-        default: lo = __builtin_amdgcn_mov_dpp((int)lo, 0x128, 0xF, 0xF, false);
-                 hi = __builtin_amdgcn_mov_dpp((int)hi, 0x128, 0xF, 0xF, false); break; // row_ror:8
-    }
-    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-__device__ inline double readlane_f64(double v, int l) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), l);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), l);
-    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-__device__ inline double wave_total_f64(double v) {
-    v += dpp_f64(v, 0);
-    v += dpp_f64(v, 1);
-    v += dpp_f64(v, 2);
-    v += dpp_f64(v, 3);
-    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-
-template <class T>
-__device__ inline T wave_inclusive_scan(T v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const T y = __shfl_up(v, off);
-        if (lane >= off) v += y;
-    }
-    return v;
 }
 
 // Lanes below this one in a 64-lane mask.
@@ -957,16 +1204,6 @@ __global__ __launch_bounds__(kThreads) void pattern_rows_kernel(
     }
 }
 
-// f(integral_constant<int, i>) for i = A .. B-1.
-template <int A, int B, class Fn>
-inline void static_for(Fn&& f) {
-    if constexpr (A < B) {
-        f(std::integral_constant<int, A>{});
-        static_for<A + 1, B>(f);
-    }
-}
-
-inline unsigned cdiv(long a, long b) { return static_cast<unsigned>((a + b - 1) / b); }
 
 }  // namespace
 
@@ -984,49 +1221,70 @@ hipError_t launch_pool(const uint16_t* q, const uint16_t* k, double* qbar, doubl
     return hipGetLastError();
 }
 
-hipError_t launch_block_mass(const double* qbar, const double* kbar, double* G, int BH,
-                             int L, int d, int bs, int n, double scale, hipStream_t s) {
-    const dim3 grid(cdiv(n, 128), cdiv(n, 128), BH);
-    if (d == 128)
-        hipLaunchKernelGGL(logits_kernel<128>, grid, dim3(kThreads), 0, s, qbar, kbar, G, n, scale);
-    else
-        hipLaunchKernelGGL(logits_kernel<64>, grid, dim3(kThreads), 0, s, qbar, kbar, G, n, scale);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mass_softmax_kernel, dim3((unsigned)BH * n), dim3(kThreads), 0, s, G, L,
-                       bs, n);
-    return hipGetLastError();
+hipError_t launch_logits(const double* qbar, const double* kbar, double* G, int BH, int d, int n, double scale,
+                         hipStream_t s) {
+    auto go = [&](auto kern, int T) {
+        hipLaunchKernelGGL(kern, dim3(cdiv(n, T), cdiv(n, T), (unsigned)BH), dim3(kThreads), 0, s, qbar, kbar, G, n,
+                           scale);
+        return hipGetLastError();
+    };
+    // 64 x 64 tiles while they fill the chip twice, else 32 x 32
+    const bool fills = (long)BH * cdiv(n, 64) * cdiv(n, 64) >= 512;
+    if (d == 128) return fills ? go(logits_kernel<128, 64>, 64) : go(logits_kernel<128, 32>, 32);
+    return fills ? go(logits_kernel<64, 64>, 64) : go(logits_kernel<64, 32>, 32);
 }
 
-hipError_t launch_rhs(const double* G, const int* reg, double* r, double* part, int BH, int n, int F,
-                      hipStream_t s) {
-    hipLaunchKernelGGL(rhs_kernel, dim3(cdiv(3 * n - 1, kThreads), kRhsChunks, BH), dim3(kThreads), 0, s, G, part,
-                       BH, n);
-    hipError_t e = hipGetLastError();
+// Rows per work-group of map_sums_kernel: few enough that four work-groups per
+// compute unit share a small map's rows (a group's rows are a serial chain),
+// 16 otherwise (each chunk adds 2n partial sums to write and read).  4 heads
+// of 300 blocks, whole prediction: 83, 67 and 59 us with 32, 16 and 8 rows;
+// 24 heads of 929: 574, 565 and 573.
+static int sum_rows(int BH, int n) {
+    int R = kMaxSumRows;
+    while (R > 4 && (long)BH * cdiv(n, R) < 1024) R /= 2;
+    return R;
+}
+
+size_t fit_part_doubles(int BH, int n) {
+    const int R = sum_rows(BH, n);
+    return (size_t)BH * cdiv(n, R) * (2 * (size_t)n + R - 1);
+}
+
+hipError_t launch_fit(double* G, bool logits, const int* reg, const double* Sinv, double* part, double* r, double* bU,
+                      double* u, double* X, int BH, int L, int bs, int n, int F, hipStream_t s) {
+    // the whole fit in one launch while a head's map fits the LDS
+    auto small = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)BH), dim3(kFitThreads), 0, s, G, reg, Sinv, X, L, bs, n, F);
+        return hipGetLastError();
+    };
+    if (n <= 64 && F <= 64) return logits ? small(fit_small_kernel<64, true>) : small(fit_small_kernel<64, false>);
+    if (n <= 128 && F <= 128) return logits ? small(fit_small_kernel<128, true>) : small(fit_small_kernel<128, false>);
+
+    const int q = n - 1 + F, R = sum_rows(BH, n), nch = (int)cdiv(n, R);
+    hipError_t e = hipErrorInvalidValue;
+    const int ept = (n + kThreads - 1) / kThreads;
+    static_for<1, kMaxBlocks / kThreads + 1>([&](auto w) {
+        constexpr int EPT = decltype(w)::value;
+        if (ept != EPT) return;
+        auto kern = logits ? map_sums_kernel<EPT, true> : map_sums_kernel<EPT, false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)nch, (unsigned)BH), dim3(kThreads), 0, s, G, part, L, bs, n, R);
+        e = hipGetLastError();
+    });
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rhs_sum_kernel, dim3(cdiv(3 * n - 1, kThreads), BH), dim3(kThreads), 0, s, part, r, BH, n, F);
+    hipLaunchKernelGGL(rhs_kernel, dim3(cdiv(3 * n - 1, kThreads) + (unsigned)F, (unsigned)BH), dim3(kThreads), 0, s,
+                       part, G, reg, r, n, F, nch, R);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rhs_frame_kernel, dim3(F, BH), dim3(kThreads), 0, s, G, reg, r, n, F);
-    return hipGetLastError();
-}
-
-hipError_t launch_solve(const double* r, const int* reg, const double* Sinv, double* bU,
-                        double* u, double* X, int BH, int n, int F, hipStream_t s) {
-    const int q = n - 1 + F;
     hipLaunchKernelGGL(solve_pre_kernel, dim3(cdiv(q, kThreads), BH), dim3(kThreads),
                        (size_t)(2 * n - 1) * sizeof(double), s, r, reg, bU, n, F);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(solve_gemv_kernel, dim3(cdiv(q, 64), kSolveSplit), dim3(kThreads), 0, s, Sinv, bU,
                        u, q, BH);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(solve_post_kernel, dim3(BH), dim3(kThreads), (size_t)q * sizeof(double) + (size_t)F * sizeof(int),
-                       s, r, u, reg, X, n, F, BH);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(solve_gauge_kernel, dim3(BH), dim3(kThreads), 0, s, X, n, F);
+    hipLaunchKernelGGL(solve_post_kernel, dim3(BH), dim3(kPostThreads),
+                       (size_t)q * sizeof(double) + (size_t)F * sizeof(int), s, r, u, reg, X, n, F, BH);
     return hipGetLastError();
 }
 
