@@ -246,12 +246,12 @@ __device__ __forceinline__ void static_for(F&& f) {
 //   lists  per XCD, the items of its ranges in head-major order (a chunk
 //          item is the slot number with bit 30 set), its length, start and
 //          a zeroed fetch counter; each list is then bucket-sorted by
-//          decreasing cost (lists longer than kPlanSortMax keep the head
-//          order), so long items start early instead of ending the launch
-//          late.
+//          decreasing cost, in head order within a bucket (lists longer than
+//          kPlanSortMax keep the head order), so long items start early
+//          instead of ending the launch late.
 // Every work-group computes the same split decision and slot numbering from
-// the same counts, so the plan is deterministic; only the order of equal-
-// cost items within a bucket varies, which affects timing, not results.
+// the same counts, so the plan is deterministic (but for the order of the 64
+// equal-cost items that one wave places at once, which affects timing only).
 // The attention work-groups are persistent (one per CU): a work-group
 // fetches the next item of its XCD's list with an atomic counter and, once
 // that list is drained, of the other XCDs' lists, until all are drained.
@@ -335,9 +335,14 @@ __device__ T plan_scan(T v, T* buf, T& total) {
     return base + incl - v;
 }
 
+// Sums over all pairs are 32-bit (Acc) while they fit, and nothing of the
+// split is computed when no pair is dear enough: the passes are chains of
+// integer instructions in 16 waves (11,820 pairs: 44 us with 64-bit sums and
+// an unordered sort, 33 us; 12 us at 1395 pairs).
+template <class Acc>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __restrict__ kv_cnt, void* ws,
                                                             int BH, int n, int ncu, int S) {
-    __shared__ long long scan64[kPlanThreads / 64];
+    __shared__ Acc scanw[kPlanThreads / 64];
     __shared__ int scan32[kPlanThreads / 64];
     __shared__ int xcnt[kXcds];
     __shared__ uint32_t cache[kPlanCache];   // both counts of a pair, 16 bits each
@@ -346,62 +351,67 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     const long long P = (long long)BH * npairs;
     const Plan pl(ws, BH, npairs, S);
     long long* hp = pl.headpre + (size_t)x * (BH + 1);
-    const long long per = (P + kPlanThreads - 1) / kPlanThreads;
-    const long long q0 = min(P, (long long)t * per), q1 = min(P, q0 + per);
+    // pair numbers fit 32 bits (the item words hold them)
+    const int per = (int)((P + kPlanThreads - 1) / kPlanThreads);
+    const int q0 = (int)min(P, (long long)t * per), q1 = (int)min(P, (long long)q0 + per);
     struct Pair { int c0, c1; };
-    auto load_counts = [&](long long q) {
-        const int bh = (int)(q / npairs), p = (int)(q % npairs);
+    auto load_counts = [&](int q) {
+        const int bh = q / npairs, p = q % npairs;
         const size_t r0 = (size_t)bh * n + 2 * p;
         return Pair{clamp_count(kv_cnt, r0, n), 2 * p + 1 < n ? clamp_count(kv_cnt, r0 + 1, n) : 0};
     };
     // head and pair index of q0, advanced pair by pair in the loops below
     // (no division per pair)
-    const int h0 = (int)(q0 / npairs), p0 = (int)(q0 % npairs);
+    const int h0 = q0 / npairs, p0 = q0 % npairs;
     // every pass reads the counts: from LDS when they fit (loaded once,
     // coalesced), else from the lists' counts in memory
     const bool cached = P <= kPlanCache;
     if (cached) {
-        // every thread's loads issued at once (indices clamped to the last
-        // pair, so that no load sits behind a branch), then stored
-        constexpr int FILL = kPlanCache / kPlanThreads;
+        // a thread's loads issued four rounds at once (indices clamped to the
+        // last pair, so that no load sits behind a branch), then stored
         const int Pi = (int)P;
-        int c0[FILL], c1[FILL];
+        for (int b0 = 0; b0 < Pi; b0 += 4 * kPlanThreads) {
+            int c0[4], c1[4];
 #pragma unroll
-        for (int u = 0; u < FILL; ++u) {
-            const int q = min(t + u * kPlanThreads, Pi - 1);
-            const int bh = q / npairs, pp = q - bh * npairs;
-            const size_t r0 = (size_t)bh * n + 2 * pp;
-            c0[u] = kv_cnt[r0];
-            c1[u] = kv_cnt[2 * pp + 1 < n ? r0 + 1 : r0];
-        }
+            for (int u = 0; u < 4; ++u) {
+                const int q = min(b0 + t + u * kPlanThreads, Pi - 1);
+                const int bh = q / npairs, pp = q - bh * npairs;
+                const size_t r0 = (size_t)bh * n + 2 * pp;
+                c0[u] = kv_cnt[r0];
+                c1[u] = kv_cnt[2 * pp + 1 < n ? r0 + 1 : r0];
+            }
 #pragma unroll
-        for (int u = 0; u < FILL; ++u) {
-            const int q = t + u * kPlanThreads;
-            const int pp = q % npairs;
-            const int a = min(max(c0[u], 0), n), b = 2 * pp + 1 < n ? min(max(c1[u], 0), n) : 0;
-            if (q < Pi) cache[q] = (uint32_t)a | ((uint32_t)b << 16);
+            for (int u = 0; u < 4; ++u) {
+                const int q = b0 + t + u * kPlanThreads;
+                const int pp = q % npairs;
+                const int a = min(max(c0[u], 0), n), b = 2 * pp + 1 < n ? min(max(c1[u], 0), n) : 0;
+                if (q < Pi) cache[q] = (uint32_t)a | ((uint32_t)b << 16);
+            }
         }
         __syncthreads();
     }
-    auto counts = [&](long long q) {
+    auto counts = [&](int q) {
         if (cached) {
             const uint32_t v = cache[q];
             return Pair{(int)(v & 0xFFFF), (int)(v >> 16)};
         }
         return load_counts(q);
     };
-    // cost before every pair (global order) and before every head
-    long long mine = 0;
-    for (long long q = q0; q < q1; ++q) {
+    // cost before every pair (global order) and before every head; the
+    // dearest pair
+    Acc mine = 0;
+    int dearest = 0;
+    for (int q = q0; q < q1; ++q) {
         const Pair c = counts(q);
         mine += 4 + c.c0 + c.c1;
+        dearest = max(dearest, 4 + c.c0 + c.c1);
     }
-    long long W = 0;
-    const long long pre = plan_scan<long long>(mine, scan64, W);
+    Acc W = 0;
+    const Acc pre = plan_scan<Acc>(mine, scanw, W);
     {
-        long long run = pre;
+        Acc run = pre;
         int h = h0, pp = p0;
-        for (long long q = q0; q < q1; ++q) {
+        for (int q = q0; q < q1; ++q) {
             const Pair c = counts(q);
             if (pp == 0) hp[h] = run;
             run += 4 + c.c0 + c.c1;
@@ -409,28 +419,28 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         }
         if (t == 0) hp[BH] = W;
     }
-    __syncthreads();   // the head prefixes (this work-group's own copy) are visible
     // split policy: chunks of cs steps for pairs costing more than half the
-    // per-CU load, cs doubled until the chunks fit the slots
+    // per-group load, cs doubled until the chunks fit the slots
     const double A = (double)W / (double)max(ncu, 1);
-    long long cs = 0;
-    auto nchunks = [&](const Pair& c, long long csteps) -> long long {
-        const long long cost = 4 + c.c0 + c.c1;
-        const long long steps = max(c.c0, c.c1);
-        if (csteps <= 0 || (double)cost <= 0.5 * A || steps <= csteps) return 1;
+    const int limit = (int)min(0.5 * A, 2147483647.0);   // (a cost above half the load is above its floor)
+    int cs = 0;
+    auto nchunks = [&](const Pair& c, int csteps) {
+        const int steps = max(c.c0, c.c1);
+        if (csteps <= 0 || 4 + c.c0 + c.c1 <= limit || steps <= csteps) return 1;
         return (steps + csteps - 1) / csteps;
     };
-    if (S >= 2) {
-        cs = max((long long)kMinChunkSteps, (long long)(A / 8.0));
+    __syncthreads();   // the head prefixes (this work-group's own copy) are visible
+    if (__syncthreads_or(S >= 2 && dearest > limit)) {
+        cs = (int)min(max((double)kMinChunkSteps, floor(A / 8.0)), 2.0 * kMaxBlocks);
         for (;;) {
-            long long need = 0;
-            for (long long q = q0; q < q1; ++q) {
-                const long long C = nchunks(counts(q), cs);
+            Acc need = 0;
+            for (int q = q0; q < q1; ++q) {
+                const int C = nchunks(counts(q), cs);
                 if (C > 1) need += C;
             }
-            long long tot_need = 0;
-            (void)plan_scan<long long>(need, scan64, tot_need);
-            if (tot_need <= S) break;
+            Acc tot_need = 0;
+            (void)plan_scan<Acc>(need, scanw, tot_need);
+            if (tot_need <= (Acc)S) break;
             cs *= 2;
             if (cs > n) { cs = 0; break; }
         }
@@ -439,7 +449,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     // pair's midpoint, min(7, floor(8 mid2 / (2 tot))) counted by comparisons
     // (a head's cost is at most npairs (4 + 2n) < 2^25, so its midpoints
     // and their multiples of tot stay inside 32 bits)
-    auto xcd_of = [&](long long hb, long long tot, long long before, const Pair& c) {
+    auto xcd_of = [&](Acc hb, Acc tot, Acc before, const Pair& c) {
         const int mid4 = 4 * (2 * (int)(before - hb) + 4 + c.c0 + c.c1);
         const int tt = (int)tot;
         int xq = 0;
@@ -451,38 +461,38 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     // its range crosses into the next head
     struct HeadWalk {
         int h, pp;
-        long long hb, tot;
+        Acc hb, tot;
     };
     auto head_start = [&]() {
         HeadWalk hw{h0, p0, 0, 1};
         if (q0 < q1) {
-            hw.hb = hp[h0];
-            hw.tot = hp[h0 + 1] - hw.hb;
+            hw.hb = (Acc)hp[h0];
+            hw.tot = (Acc)hp[h0 + 1] - hw.hb;
         }
         return hw;
     };
-    auto head_next = [&](HeadWalk& hw, long long q) {
+    auto head_next = [&](HeadWalk& hw, int q) {
         if (++hw.pp == npairs) {
             hw.pp = 0;
             ++hw.h;
             if (q + 1 < q1) {
-                hw.hb = hp[hw.h];
-                hw.tot = hp[hw.h + 1] - hw.hb;
+                hw.hb = (Acc)hp[hw.h];
+                hw.tot = (Acc)hp[hw.h + 1] - hw.hb;
             }
         }
     };
     int cntx[kXcds] = {};
-    long long slots_mine = 0, splits_mine = 0;
+    int slots_mine = 0, splits_mine = 0;
     {
-        long long run = pre;
+        Acc run = pre;
         HeadWalk hw = head_start();
-        for (long long q = q0; q < q1; ++q) {
+        for (int q = q0; q < q1; ++q) {
             const Pair c = counts(q);
             const int xq = xcd_of(hw.hb, hw.tot, run, c);
             head_next(hw, q);
-            const long long C = nchunks(c, cs);
+            const int C = nchunks(c, cs);
 #pragma unroll
-            for (int xx = 0; xx < kXcds; ++xx) cntx[xx] += xx == xq ? (int)C : 0;
+            for (int xx = 0; xx < kXcds; ++xx) cntx[xx] += xx == xq ? C : 0;
             if (C > 1) {
                 slots_mine += C;
                 splits_mine += 1;
@@ -498,29 +508,32 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     int first = 0;
     for (int xx = 0; xx < x; ++xx) first += xcnt[xx];
     const int lenx = xcnt[x];
-    long long dummy = 0;
-    const long long posx = plan_scan<long long>((long long)cntx[x], scan64, dummy);
-    const long long slot0 = plan_scan<long long>(slots_mine, scan64, dummy);
-    long long nsplit = 0;
-    const long long split0 = plan_scan<long long>(splits_mine, scan64, nsplit);
+    int dummy = 0;
+    const int posx = plan_scan<int>(cntx[x], scan32, dummy);
+    int slot0 = 0, split0 = 0, nsplit = 0;
+    if (cs > 0) {   // (cs is the same in every thread)
+        slot0 = plan_scan<int>(slots_mine, scan32, dummy);
+        split0 = plan_scan<int>(splits_mine, scan32, nsplit);
+    }
     // this XCD's items, head-major; the chunks of a split pair described
     {
-        long long run = pre, pos = first + posx, slot = slot0, sidx = split0;
+        Acc run = pre;
+        int pos = first + posx, slot = slot0, sidx = split0;
         HeadWalk hw = head_start();
-        for (long long q = q0; q < q1; ++q) {
+        for (int q = q0; q < q1; ++q) {
             const Pair c = counts(q);
             const int xq = xcd_of(hw.hb, hw.tot, run, c);
             head_next(hw, q);
-            const long long C = nchunks(c, cs);
+            const int C = nchunks(c, cs);
             if (C == 1) {
-                if (xq == x) pl.items[pos++] = (int)q;
+                if (xq == x) pl.items[pos++] = q;
             } else {
-                const long long steps = max(c.c0, c.c1);
+                const int steps = max(c.c0, c.c1);   // cc * steps < 2^25
                 if (xq == x) {
-                    pl.splits[sidx] = make_int4((int)q, (int)C, (int)slot, 0);
-                    for (long long cc = 0; cc < C; ++cc) {
-                        pl.chunks[slot + cc] = make_int4((int)q, (int)(cc * steps / C), (int)((cc + 1) * steps / C), 0);
-                        pl.items[pos++] = kChunkBit | (int)(slot + cc);
+                    pl.splits[sidx] = make_int4(q, C, slot, 0);
+                    for (int cc = 0; cc < C; ++cc) {
+                        pl.chunks[slot + cc] = make_int4(q, cc * steps / C, (cc + 1) * steps / C, 0);
+                        pl.items[pos++] = kChunkBit | (slot + cc);
                     }
                 }
                 slot += C;
@@ -534,15 +547,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         pl.start[x] = first;
         pl.ctr[kCtrStride * x] = 0;
         if (x == 0) {
-            pl.misc[0] = (int)nsplit;
-            pl.misc[1] = (int)cs;
+            pl.misc[0] = nsplit;
+            pl.misc[1] = cs;
         }
     }
-    // Longest items first: a bucket sort of the list by decreasing cost
-    // (order within a bucket unspecified; the order only affects timing).
+    // Longest items first: a bucket sort of the list by decreasing cost, in
+    // head order within a bucket (the order only affects timing: items of
+    // equal cost out of head order lose K/V locality, 0.7% of a launch whose
+    // rows all keep 30 of 591 blocks).  Each wave takes a contiguous part of
+    // the list and has its own cursors.
     if (lenx > kPlanSortMax) return;
     __shared__ int vals[kPlanSortMax];
-    __shared__ int cursor[kPlanBuckets];
+    constexpr int PW = kPlanThreads / 64;
+    __shared__ int cursor[PW][kPlanBuckets];
     int shift = 0;
     while (((4 + 2 * n) >> shift) >= kPlanBuckets) ++shift;
     auto bucket = [&](int item) {
@@ -556,26 +573,53 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         }
         return (kPlanBuckets - 1) - min(kPlanBuckets - 1, c >> shift);   // descending cost
     };
-    for (int bb = t; bb < kPlanBuckets; bb += kPlanThreads) cursor[bb] = 0;
+    for (int bb = t; bb < PW * kPlanBuckets; bb += kPlanThreads) cursor[bb / kPlanBuckets][bb % kPlanBuckets] = 0;
     __syncthreads();   // also: every item (and chunk) of the list has been written
-    for (int a = t; a < lenx; a += kPlanThreads) {
+    const int wv = t >> 6, part = (lenx + kPlanThreads - 1) / kPlanThreads * 64;
+    const int a0 = wv * part + (t & 63), a1 = min(lenx, (wv + 1) * part);
+    for (int a = a0; a < a1; a += 64) {
         const int it = pl.items[first + a];
         vals[a] = it;
-        atomicAdd(&cursor[bucket(it)], 1);
+        atomicAdd(&cursor[wv][bucket(it)], 1);
     }
     __syncthreads();
-    {   // exclusive scan of the bucket sizes (kPlanBuckets <= kPlanThreads entries)
+    {   // exclusive scan of the bucket sizes (one bucket per thread), then of the waves' shares
         static_assert(kPlanBuckets <= kPlanThreads, "one bucket per thread");
-        const int c = t < kPlanBuckets ? cursor[t] : 0;
-        int all = 0;
-        const int ex = plan_scan<int>(c, scan32, all);
-        if (t < kPlanBuckets) cursor[t] = ex;
+        int c = 0, all = 0;
+        if (t < kPlanBuckets)
+            for (int ww = 0; ww < PW; ++ww) c += cursor[ww][t];
+        int ex = plan_scan<int>(c, scan32, all);
+        if (t < kPlanBuckets) {
+            for (int ww = 0; ww < PW; ++ww) {
+                const int share = cursor[ww][t];
+                cursor[ww][t] = ex;
+                ex += share;
+            }
+        }
     }
     __syncthreads();
-    for (int a = t; a < lenx; a += kPlanThreads) {
+    for (int a = a0; a < a1; a += 64) {
         const int it = vals[a];
-        pl.items[first + atomicAdd(&cursor[bucket(it)], 1)] = it;
+        pl.items[first + atomicAdd(&cursor[wv][bucket(it)], 1)] = it;
     }
+}
+
+// The plan of a launch whose work-groups are all resident at once with one
+// item each and nothing to split (P <= resident groups <= kPlanThreads x 4, no
+// slots): neither order nor balance can change its end, so the lists are the
+// pairs in order, an eighth per XCD, and the counts are not read.  256 pairs:
+// 17 us with plan_kernel, 5 with this (16 pairs: 15 and 1.4).
+__global__ __launch_bounds__(kPlanThreads) void plan_small_kernel(void* ws, int BH, int npairs) {
+    const Plan pl(ws, BH, npairs, 0);
+    const int P = BH * npairs, t = threadIdx.x;
+    for (int q = t; q < P; q += kPlanThreads) pl.items[q] = q;
+    if (t < kXcds) {
+        const int first = t * P / kXcds;
+        pl.start[t] = first;
+        pl.len[t] = (t + 1) * P / kXcds - first;
+        pl.ctr[kCtrStride * t] = 0;
+    }
+    if (t < 2) pl.misc[t] = 0;
 }
 
 // Merge of split pairs: for every row of both query blocks of a split pair,
@@ -1736,8 +1780,16 @@ hipError_t launch(const uint16_t* q, const uint16_t* k, const uint16_t* v, const
                   void* ws, int S, hipStream_t s) {
     const int ncu = persistent_groups();
     const int slots = ncu * kGroupsPerCu<D, BS>;   // work-groups resident at once
-    hipLaunchKernelGGL(plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
-    const long items = (long)BH * ((n + 1) / 2) + S;
+    const int npairs = (n + 1) / 2;
+    const long P = (long)BH * npairs;
+    if (S == 0 && P <= slots)
+        hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3(kPlanThreads), 0, s, ws, BH, npairs);
+    else if (P * (4 + 2L * n) < (1L << 31))
+        hipLaunchKernelGGL(plan_kernel<int>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
+    else
+        hipLaunchKernelGGL(plan_kernel<long long>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots,
+                           S);
+    const long items = P + S;
     const unsigned groups = (unsigned)std::min<long>(slots, items);
     if constexpr (D * BS == 128 * 128)
         hipLaunchKernelGGL((attn_fwd_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,

@@ -85,3 +85,50 @@ def test_attention_narrow_tiles_edges(d, bs, tail):
     lse = torch.full((1, H, L), float("nan"), dtype=torch.float32, device="cuda")
     M.mod_block_sparse_attn_fwd(M.make_shape(1, H, L, d, bs), q, k, v, idx.cuda(), cnt.cuda(), 0.0, o, lse)
     _check_rows(host, [pick], o, lse, d, bs, L, [(0, h) for h in range(H)], list(range(n)))
+
+
+@pytest.mark.parametrize("d,bs,n", [(128, 128, 101), (64, 64, 64), (128, 64, 33)])
+def test_attention_plan_without_counts(d, bs, n):
+    """Fewer items than resident groups and no slots (short sequences, or a
+    plan-only workspace): the plan in order, uneven and empty rows, on a
+    workspace of exactly the plan's size with stale contents."""
+    H, L = 2, (n - 1) * bs + 17
+    host, (q, k, v) = _layer(1, H, L, d, n)
+    rows, idx, cnt = _uneven_lists(1, H, n, n)
+    shape = M.make_shape(1, H, L, d, bs)
+    size = M.mod_attn_plan_bytes(shape)
+    ws = torch.full((size + 64,), 0x5A, dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((1, H, L), float("nan"), dtype=torch.float32, device="cuda")
+        M.mod_block_sparse_attn_fwd(shape, q, k, v, idx, cnt, 0.0, o, lse, ws, size)
+        _check_rows(host, rows, o, lse, d, bs, L, [(0, 0), (0, 1)], sorted({0, 1, 2, n // 2, n - 2, n - 1}))
+    assert (ws[size:] == 0x5A).all()
+
+
+def test_attention_plan_of_sums_beyond_32_bits():
+    """512 heads of 2048 blocks: the plan's sums over all pairs need 64 bits.
+    Every row keeps its own block, the next one and a few full rows all."""
+    H, n, d, bs = 512, 2048, 64, 64
+    L = n * bs
+    assert H * (n // 2) * (4 + 2 * n) >= 2**31
+    host, small = _layer(1, 1, L, d, 3)
+    q, k, v = (x.expand(1, H, L, d).contiguous() for x in small)
+    own = torch.arange(n, dtype=torch.int32)
+    row = torch.stack([own, (own + 1) % n], 1).sort(1).values.cuda()
+    idx = torch.zeros((1, H, n, n), dtype=torch.int32, device="cuda")
+    idx[..., :2] = row
+    cnt = torch.full((1, H, n), 2, dtype=torch.int32, device="cuda")
+    full = [0, 777, n - 1]
+    for i in full:
+        idx[:, :, i] = own.cuda()
+        cnt[:, :, i] = n
+    o = torch.empty_like(q)
+    lse = torch.empty((1, H, L), dtype=torch.float32, device="cuda")
+    shape = M.make_shape(1, H, L, d, bs)
+    ws = torch.empty(M.mod_attn_plan_bytes(shape), dtype=torch.uint8, device="cuda")
+    M.mod_block_sparse_attn_fwd(shape, q, k, v, idx, cnt, 0.0, o, lse, ws, ws.numel())
+    rows = [[list(range(n)) if i in full else sorted({i, (i + 1) % n}) for i in range(n)]]
+    for h in (0, 200, H - 1):
+        _check_rows(host, [rows], o[:, h:h + 1], lse[:, h:h + 1], d, bs, L, [(0, 0)], [0, 1, 776, 777, 1500, n - 1])
+    assert torch.equal(o[0, 1].view(torch.int16), o[0, H - 1].view(torch.int16))
