@@ -1838,7 +1838,7 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt,
     const float* __restrict__ lse, float scale, float log_eta, double* __restrict__ stat, int L, int n,
-    int nv) {
+    int nv, int chunks) {
     constexpr int QW = BS / 32;        // waves per group, 32 query rows each
     constexpr int NT = BS * 4;         // two groups
     constexpr int RT = BS / 32;        // 32-row kv sub-tiles per tile
@@ -1853,7 +1853,8 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
     __shared__ int part[2][2][QW];     // [tile parity][group][wave] counts
 
     const int npv = (nv + 1) / 2;      // pairs of video rows
-    const int bh = blockIdx.x / npv, pr = blockIdx.x % npv;
+    const int ch = blockIdx.x % chunks, pair = blockIdx.x / chunks;
+    const int bh = pair / npv, pr = pair % npv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, l32 = lane & 31;
@@ -1864,8 +1865,11 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
     const bool row_ok = i < nv && qrow < L;
 
     const size_t row0 = (size_t)bh * n + 2 * pr;
-    const int ucnt = union_of_rows<NT>(kv_idx, kv_cnt, row0, 2 * pr + 1 < nv, n, umask, ulist, wsum, tid,
+    const int uall = union_of_rows<NT>(kv_idx, kv_cnt, row0, 2 * pr + 1 < nv, n, umask, ulist, wsum, tid,
                                        lane, w);
+    // this work-group's part of the walk
+    const int u0 = ch * uall / chunks, ucnt = (ch + 1) * uall / chunks - u0;
+    const uint32_t* const ulst = ulist + u0;
 
     bf16x8 qreg[KK];
 #pragma unroll
@@ -1965,7 +1969,7 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
         }
     };
     auto entry = [&](int t) __attribute__((always_inline)) {
-        return __builtin_amdgcn_readfirstlane(ulist[t]);
+        return __builtin_amdgcn_readfirstlane(ulst[t]);
     };
 
     if (ucnt > 0) copy.issue_all(kg, (int)(entry(0) & 0xFFFF), L, kbuf[0], w, lane);
@@ -1990,7 +1994,7 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
     // the part of an interval both groups run first and last
     auto begin = [&](int t) __attribute__((always_inline)) {
         if (t + 1 < ucnt) copy.issue_all(kg, (int)(e1 & 0xFFFF), L, kbuf[(t + 1) & 1], w, lane);
-        return ulist[min(t + 2, max(ucnt - 1, 0))];
+        return ulst[min(t + 2, max(ucnt - 1, 0))];
     };
     auto end = [&](int t, uint32_t e2v) __attribute__((always_inline)) {
 #pragma unroll
@@ -2047,8 +2051,18 @@ hipError_t launch_count(const uint16_t* q, const uint16_t* k, const int32_t* kv_
                         const float* lse, float scale, float log_eta, double* stat, int BH, int L, int n,
                         int nv, hipStream_t s) {
     const unsigned npv = (unsigned)(nv + 1) / 2;
-    hipLaunchKernelGGL((stat_count_kernel<D, BS>), dim3((unsigned)BH * npv), dim3(BS * 4), 0, s, q, k, kv_idx,
-                       kv_cnt, lse, scale, log_eta, stat, L, n, nv);
+    // Every listed block is counted by itself, so a walk may be cut anywhere:
+    // into a power of two of parts of at least 16 blocks, until there are 16
+    // work-groups per compute unit, which leaves a last round of a few percent
+    // (3 heads of 929 blocks, dense: 1395 whole walks took six rounds of 256
+    // units for 5.4 rounds of work, 8.77 ms; 8.23 with four parts of each).  The
+    // parts of a pair are neighbouring work-groups, so an XCD sees the same
+    // part of every walk and keeps its K tiles (three parts: 8.68 ms).
+    const long groups = (long)BH * npv, want = 16L * persistent_groups();
+    int chunks = 1;
+    while (groups * chunks < want && n / (2 * chunks) >= 16) chunks *= 2;
+    hipLaunchKernelGGL((stat_count_kernel<D, BS>), dim3((unsigned)(groups * chunks)), dim3(BS * 4), 0, s, q, k,
+                       kv_idx, kv_cnt, lse, scale, log_eta, stat, L, n, nv, chunks);
     return hipGetLastError();
 }
 
