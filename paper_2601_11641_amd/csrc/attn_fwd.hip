@@ -604,24 +604,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     }
 }
 
-// The plan of a launch whose work-groups are all resident at once with one
-// item each and nothing to split (P <= resident groups <= kPlanThreads x 4, no
-// slots): neither order nor balance can change its end, so the lists are the
-// pairs in order, an eighth per XCD, and the counts are not read.  256 pairs:
-// 17 us with plan_kernel, 5 with this (16 pairs: 15 and 1.4).
-__global__ __launch_bounds__(kPlanThreads) void plan_small_kernel(void* ws, int BH, int npairs) {
-    const Plan pl(ws, BH, npairs, 0);
-    const int P = BH * npairs, t = threadIdx.x;
-    for (int q = t; q < P; q += kPlanThreads) pl.items[q] = q;
-    if (t < kXcds) {
-        const int first = t * P / kXcds;
-        pl.start[t] = first;
-        pl.len[t] = (t + 1) * P / kXcds - first;
-        pl.ctr[kCtrStride * t] = 0;
-    }
-    if (t < 2) pl.misc[t] = 0;
-}
-
 // Merge of split pairs: for every row of both query blocks of a split pair,
 // LSE = log sum_c exp(lse_c) and O = sum_c exp(lse_c - LSE) O_c over its
 // chunks c = 0 .. C-1 in order (rows no chunk reached: O = 0, LSE = -inf).
@@ -698,14 +680,24 @@ __device__ __forceinline__ int fetch_item(const Plan& pl, int x) {
     return -1;
 }
 
+// The one item of work-group `group` in a launch without a plan (every pair
+// has a resident work-group of its own and nothing is split, so neither order
+// nor balance can change the launch's end): an eighth of the P pairs per XCD,
+// in order; -1 for the groups that fill up the grid.
+__device__ __forceinline__ int direct_item(int P, int group) {
+    const int x = group % kXcds, first = x * P / kXcds, item = first + group / kXcds;
+    return item < (x + 1) * P / kXcds ? item : -1;
+}
+
 // The next item of this work-group into item_s = {pair, first step, end
 // step, slot (-1: whole pair)}; pair -1 ends the work-group, -2 is skipped.
 // One thread calls it.  (attn_fwd_kernel spells the same steps out: called
 // from there, the function cost 0.8% at 720p through another register
 // assignment.)
+template <bool DIRECT>
 __device__ __forceinline__ void take_item(void* ws, int BH, int npairs, int S, int* item_s) {
     const Plan pl(ws, BH, npairs, S);
-    const int it = fetch_item(pl, blockIdx.x % kXcds);
+    const int it = DIRECT ? direct_item(BH * npairs, blockIdx.x) : fetch_item(pl, blockIdx.x % kXcds);
     int4 desc = make_int4(it, 0, 0x7fffffff, -1);
     if (it >= 0 && (it & kChunkBit)) {
         const int k2 = it & (kChunkBit - 1);
@@ -915,7 +907,9 @@ __device__ __forceinline__ void store_row(const f32x16 (&oacc)[D / 32], float m,
 template <int D, int BS>
 constexpr int kGroupsPerCu = D * BS == 128 * 128 ? 1 : (D * BS == 64 * 64 ? 4 : 2);
 
-template <int D, int BS>
+// DIRECT: a launch without a plan (a kernel of its own: the choice at run
+// time cost the planned launches 0.5% through the register assignment).
+template <int D, int BS, bool DIRECT>
 __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ kv_idx,
@@ -959,7 +953,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     const int npairs = (n + 1) / 2;
     if (tid == 0) {
         const Plan pl(wsi, BH, npairs, S);
-        const int it = fetch_item(pl, blockIdx.x % kXcds);
+        const int it = DIRECT ? direct_item(BH * npairs, blockIdx.x) : fetch_item(pl, blockIdx.x % kXcds);
         int4 desc = make_int4(it, 0, 0x7fffffff, -1);
         if (it >= 0 && (it & kChunkBit)) {
             const int k2 = it & (kChunkBit - 1);
@@ -1428,6 +1422,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
     l += __shfl_xor(l, 32);
     if (i < n && qrow < L)
         store_row<D, BS>(oacc, m, l, scale, slot, g, qw, l32, h, base, bh, qrow, L, o, lse, wsi, BH, npairs, S);
+    if constexpr (DIRECT) break;
     }   // next item
 }
 
@@ -1458,7 +1453,7 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
 template <int D, int BS>
 constexpr int kNarrowWaves = D == 64 ? 4 : 2;   // waves per SIMD
 
-template <int D, int BS>
+template <int D, int BS, bool DIRECT>
 __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ kv_idx,
@@ -1487,7 +1482,7 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));   // per-item values are not hoisted out of the loop
     const int npairs = (n + 1) / 2;
-    if (tid == 0) take_item(ws, BH, npairs, S, item_s);
+    if (tid == 0) take_item<DIRECT>(ws, BH, npairs, S, item_s);
     __syncthreads();
     const int item = item_s[0];
     const int step0 = item_s[1], step1 = item_s[2], slot = item_s[3];
@@ -1755,6 +1750,7 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
     l += __shfl_xor(l, 32);
     if (i < n && qrow < L)
         store_row<D, BS>(oacc, m, l, scale, slot, g, qw, l32, h, base, bh, qrow, L, o, lse, ws, BH, npairs, S);
+    if constexpr (DIRECT) break;
     }   // next item
 }
 
@@ -1780,23 +1776,29 @@ hipError_t launch(const uint16_t* q, const uint16_t* k, const uint16_t* v, const
                   void* ws, int S, hipStream_t s) {
     const int ncu = persistent_groups();
     const int slots = ncu * kGroupsPerCu<D, BS>;   // work-groups resident at once
-    const int npairs = (n + 1) / 2;
-    const long P = (long)BH * npairs;
-    if (S == 0 && P <= slots)
-        hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3(kPlanThreads), 0, s, ws, BH, npairs);
-    else if (P * (4 + 2L * n) < (1L << 31))
+    const long P = (long)BH * ((n + 1) / 2);
+    auto attend = [&](auto direct, unsigned groups) {
+        constexpr bool DIRECT = decltype(direct)::value;
+        if constexpr (D * BS == 128 * 128)
+            hipLaunchKernelGGL((attn_fwd_kernel<D, BS, DIRECT>), dim3(groups), dim3(BS * 4), 0, s,
+                               q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
+        else
+            hipLaunchKernelGGL((attn_narrow_kernel<D, BS, DIRECT>), dim3(groups), dim3(BS * 4), 0, s,
+                               q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
+    };
+    if (S == 0 && P <= slots) {
+        // one item per resident work-group and nothing to split: no plan (8
+        // heads of 64 blocks, 25% kept: 97 us, 80 with a plan that only numbers
+        // the pairs, 74.5 without)
+        attend(std::true_type{}, (unsigned)((P + kXcds - 1) / kXcds * kXcds));
+        return hipGetLastError();
+    }
+    if (P * (4 + 2L * n) < (1L << 31))
         hipLaunchKernelGGL(plan_kernel<int>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
     else
         hipLaunchKernelGGL(plan_kernel<long long>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots,
                            S);
-    const long items = P + S;
-    const unsigned groups = (unsigned)std::min<long>(slots, items);
-    if constexpr (D * BS == 128 * 128)
-        hipLaunchKernelGGL((attn_fwd_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
-                           q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
-    else
-        hipLaunchKernelGGL((attn_narrow_kernel<D, BS>), dim3(groups), dim3(BS * 4), 0, s,
-                           q, k, v, kv_idx, kv_cnt, scale, o, lse, L, n, ws, BH, S);
+    attend(std::false_type{}, (unsigned)std::min<long>(slots, P + S));
     if (S > 0)
         hipLaunchKernelGGL((merge_kernel<D, BS>), dim3((unsigned)(2 * ncu)), dim3(256), 0, s, ws, BH, n, S, L, o,
                            lse);

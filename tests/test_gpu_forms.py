@@ -90,8 +90,8 @@ def test_attention_narrow_tiles_edges(d, bs, tail):
 @pytest.mark.parametrize("d,bs,n", [(128, 128, 101), (64, 64, 64), (128, 64, 33)])
 def test_attention_plan_without_counts(d, bs, n):
     """Fewer items than resident groups and no slots (short sequences, or a
-    plan-only workspace): the plan in order, uneven and empty rows, on a
-    workspace of exactly the plan's size with stale contents."""
+    plan-only workspace): one item per group without a plan, uneven and empty
+    rows, on a workspace of exactly the plan's size with stale contents."""
     H, L = 2, (n - 1) * bs + 17
     host, (q, k, v) = _layer(1, H, L, d, n)
     rows, idx, cnt = _uneven_lists(1, H, n, n)
