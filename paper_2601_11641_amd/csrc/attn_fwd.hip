@@ -400,11 +400,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     // cost before every pair (global order) and before every head; the
     // dearest pair
     Acc mine = 0;
-    int dearest = 0;
+    int dearest = 0, longest = 0;
     for (int q = q0; q < q1; ++q) {
         const Pair c = counts(q);
         mine += 4 + c.c0 + c.c1;
         dearest = max(dearest, 4 + c.c0 + c.c1);
+        longest = max(longest, max(c.c0, c.c1));
     }
     Acc W = 0;
     const Acc pre = plan_scan<Acc>(mine, scanw, W);
@@ -443,6 +444,64 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
             if (tot_need <= (Acc)S) break;
             cs *= 2;
             if (cs > n) { cs = 0; break; }
+        }
+        // A launch of a few items per work-group ends with whole rounds of its
+        // long items: compare the shortest chunks with the longest walk in
+        // one, two, three or four equal parts, each by its rounds of items of
+        // at least half the longest one's steps (and five steps' worth of
+        // start), and keep the best (one head of 195 blocks, 90% kept: 98
+        // walks of 176 steps, in three parts two rounds of 59 steps, in two
+        // parts one of 88: 377 -> 305 us; the comparison costs 5 us).
+        if (cs == kMinChunkSteps && P <= 4096) {
+            constexpr int NC = 5;   // candidate 0: as above; x > 0: the longest walk in x parts
+            __shared__ int most, sums[NC];
+            if (t == 0) most = 0;
+            if (t < NC) sums[t] = 0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+            __syncthreads();
+            if ((t & 63) == 0) atomicMax(&most, longest);
+            __syncthreads();
+            const int walk = most;
+            // tot: long items, and chunks from bit 16.  Candidate 0's chunks are
+            // at most the steps of the launch / 64 and one more per pair, and
+            // its load per group, under 8 x 64, leaves under 2^18 steps; the
+            // others' are at most 4 per pair: neither half overflows.
+            int csx[NC], len[NC], tot[NC] = {};
+#pragma unroll
+            for (int x = 0; x < NC; ++x) {
+                csx[x] = max(1, x == 0 ? cs : (walk + x - 1) / x);
+                const int parts = (walk + csx[x] - 1) / csx[x];
+                len[x] = (walk + parts - 1) / max(1, parts);
+            }
+            for (int q = q0; q < q1; ++q) {
+                const Pair c = counts(q);
+                const int steps = max(c.c0, c.c1);
+#pragma unroll
+                for (int x = 0; x < NC; ++x) {
+                    const int C = nchunks(c, csx[x]);
+                    tot[x] += (C > 1 ? C << 16 : 0) + (2 * steps >= C * len[x] ? C : 0);
+                }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                for (int x = 0; x < NC; ++x) tot[x] += __shfl_xor(tot[x], off);
+            if ((t & 63) == 0) {
+#pragma unroll
+                for (int x = 0; x < NC; ++x) atomicAdd(&sums[x], tot[x]);
+            }
+            __syncthreads();
+            long long best = 0x7fffffffffffffffll;
+#pragma unroll
+            for (int x = 0; x < NC; ++x) {
+                const int all = sums[x];
+                const long long est = (long long)(((all & 0xFFFF) + ncu - 1) / ncu) * (len[x] + 5);
+                if (csx[x] >= kMinChunkSteps && (all >> 16) <= S && est < best) {
+                    best = est;
+                    cs = csx[x];
+                }
+            }
         }
     }
     // XCD of every pair: its head's cost range (from hb, tot long), by the

@@ -16,7 +16,7 @@ import workloads as W
 from parity import LSE_ABS, MAX_ABS, MEAN_ABS, attention_errors, bf16_tensor, bf16_to_f64
 
 import paper_2601_11641_amd as M
-from test_gpu_parity import _uneven_lists
+from test_gpu_parity import PLAN_MISC_INT, _uneven_lists
 
 torch = pytest.importorskip("torch")
 pytestmark = [pytest.mark.gpu,
@@ -132,3 +132,26 @@ def test_attention_plan_of_sums_beyond_32_bits():
     for h in (0, 200, H - 1):
         _check_rows(host, [rows], o[:, h:h + 1], lse[:, h:h + 1], d, bs, L, [(0, 0)], [0, 1, 776, 777, 1500, n - 1])
     assert torch.equal(o[0, 1].view(torch.int16), o[0, H - 1].view(torch.int16))
+
+
+@pytest.mark.parametrize("H,n,keep", [(1, 195, 176), (2, 131, 131)])
+def test_attention_split_in_equal_parts(H, n, keep):
+    """Few equal long walks: split into the number of parts whose rounds of
+    items end first, and merged."""
+    d = bs = 128
+    L = (n - 1) * bs + 5
+    host, (q, k, v) = _layer(1, H, L, d, n)
+    rng = np.random.default_rng(n)
+    rows = [[np.sort(rng.choice(n, size=keep, replace=False)).tolist() for _ in range(n)] for _ in range(H)]
+    idx = torch.zeros((1, H, n, n), dtype=torch.int32)
+    idx[0, :, :, :keep] = torch.tensor(rows, dtype=torch.int32)
+    cnt = torch.full((1, H, n), keep, dtype=torch.int32, device="cuda")
+    shape = M.make_shape(1, H, L, d, bs)
+    size = M.mod_attn_workspace_bytes(shape)
+    ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((1, H, L), float("nan"), dtype=torch.float32, device="cuda")
+    M.mod_block_sparse_attn_fwd(shape, q, k, v, idx.cuda(), cnt, 0.0, o, lse, ws, size)
+    split, steps = ws.view(torch.int32)[PLAN_MISC_INT:PLAN_MISC_INT + 2].cpu().tolist()
+    assert split > 0 and steps >= 64, (split, steps)
+    _check_rows(host, [rows], o, lse, d, bs, L, [(0, h) for h in range(H)], [0, 1, n // 2, n - 2, n - 1])
