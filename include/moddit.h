@@ -199,7 +199,8 @@ mod_status mod_predict_block_mask(mod_stats* stats, const void* q, const void* k
 
 /* Device workspace of the attention call, in bytes (0 for an invalid
  * shape): its work plan -- the (head, pair of query blocks) items ordered
- * and spread over the chip by their list lengths, rewritten by every call --
+ * and spread over the chip by their list lengths, rewritten by every call
+ * that needs one --
  * and room for the split-KV path (below): up to 1024 slots of partial
  * results of 8 * block * (d + 1) bytes each, fewer for short sequences
  * (none when n <= 64).  About 4 * (B*H*(n/2 + 16) + 300) bytes plus the

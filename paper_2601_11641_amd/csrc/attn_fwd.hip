@@ -234,12 +234,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 //          p goes to range floor(8 * midpoint(p) / head total)), one per XCD:
 //          neighbouring rows share K/V blocks, so an XCD's L2 serves its
 //          range, and all XCDs work through the same heads at once;
-//   split  a pair whose cost exceeds half of the average per-CU load
-//          W / (compute units) is split into C chunks of its walk (the walk
+//   split  a pair whose cost exceeds half of the average load
+//          W / (resident work-groups) is split into C chunks of its walk (the walk
 //          of a pair has max(cnt(2p), cnt(2p+1)) steps: the blocks of both
 //          lists, then the one-list blocks of both rows side by side), each
 //          of about an eighth of that load and at least kMinChunkSteps
-//          steps; the chunks become separate items writing partial results
+//          steps, or, where that is the shortest chunk, of the equal parts
+//          that end first; the chunks become separate items writing partial results
 //          (fp32 O / l and LSE per row) into workspace slots, merged after
 //          the launch in chunk order.  If the slots do not suffice, the
 //          chunk length doubles until they do (or nothing is split);
