@@ -325,8 +325,8 @@ __device__ inline double quotient(double p, double s, double inv) {
 // chunk's part of the right-hand side r = M^T vec(G).  One pass over the map
 // instead of three (softmax, diagonals, columns); every sum has a fixed order.
 // Bound by the fp64 exponentials and the map's traffic: 24 heads of 929
-// blocks (166 MB) 62 us, against 63 + 73 us for a softmax pass and
-// a pass with one thread per diagonal or column.
+// blocks (166 MB) 76 us within a layer step, against 77 + 76 us for a softmax
+// pass and a pass with one thread per diagonal or column.
 // ---------------------------------------------------------------------------
 template <int EPT, bool SOFTMAX>
 __global__ __launch_bounds__(kThreads) void map_sums_kernel(double* __restrict__ G, double* __restrict__ part,
@@ -841,7 +841,7 @@ __global__ void gate_kernel(const double* __restrict__ Xa, const double* __restr
 // built bit by bit; interpolating between the counts takes as many).  The
 // ballots that count also place the kept blocks, so the stores of a wave are
 // contiguous.  With the extrapolation: TOPK, 40 heads of 591 blocks 83 -> 44
-// us; MASS, 24 heads of 929 blocks 147 -> 85 us; bound by vector issue.
+// us; MASS, 24 heads of 929 blocks 147 -> 90 us; bound by vector issue.
 //
 // With a text segment after the video (token-type-aware masking) n counts
 // the video blocks, the lists have ldn >= n entries per row, the block tb0
