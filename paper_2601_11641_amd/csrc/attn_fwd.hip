@@ -1641,9 +1641,13 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
     };
 
     // One unit: 32 RT kv rows OFF bytes past the buffers that kad / vad
-    // address, the first `kvalid` of them inside the sequence.
+    // address, the first `kvalid` of them inside the sequence.  The softmax
+    // step covers half a tile (32 ST rows) in both parts of a walk, so a row's
+    // output depends on the blocks it walks alone, not on which of them the
+    // other row of its pair keeps too.
     auto unit = [&](auto rt_tag, auto off_tag, int kvalid) __attribute__((always_inline)) {
-        constexpr int RT = decltype(rt_tag)::value, OFF = decltype(off_tag)::value;
+        constexpr int RT = decltype(rt_tag)::value, OFF = decltype(off_tag)::value, ST = BS / 64;
+        static_assert(RT % ST == 0, "whole softmax steps");
         f32x16 sacc[RT];
         bf16x8 pb[2 * RT];
         {
@@ -1673,57 +1677,12 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
                     sacc[rt][ii] = (8 * (ii >> 2) + (ii & 3) >= lim) ? -INFINITY : sacc[rt][ii];
             }
         }
-        // the softmax step of attn_fwd_kernel: the running max is kept while
-        // no lane's probabilities of the unit sum past kSumLimit
-        float ps0, ps1;
-        auto exps = [&]() __attribute__((always_inline)) {
-            ps0 = 0.0f;
-            ps1 = 0.0f;
-#pragma unroll
-            for (int qq = 0; qq < RT * 16; ++qq) {
-                const int rt = qq / 16, c1 = (qq / 8) % 2, e = qq % 8;
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[rt][8 * c1 + e], c2, -mb));
-                pb[2 * rt + c1][e] = static_cast<__bf16>(p);
-                if (qq % 2 == 0)
-                    ps0 += p;
-                else
-                    ps1 += p;
-                if (qq % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int c = 0; c < 2 * RT; ++c) asm volatile("" : "+v"(pb[c]));
-        };
-        bool fast = __all(m > -INFINITY);
-        if (fast) {
-            exps();
-            fast = !__any(!(ps0 + ps1 <= kSumLimit));
-        }
-        if (!fast) {
-            asm volatile("" ::: "memory");
-            float mx = -INFINITY;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int ii = 0; ii < 16; ii += 2) mx = fmaxf(mx, fmaxf(sacc[rt][ii], sacc[rt][ii + 1]));
-            mx = max_across_halves(mx);
-            const float m_new = fmaxf(m, mx);
-            const float alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * c2);
-            if (__any(alpha != 1.0f)) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
-                l *= alpha;
-            }
-            m = m_new;
-            mb = m_new == -INFINITY ? 0.0f : m_new * c2;
-            exps();
-        }
-        l += ps0 + ps1;
-        asm volatile("" : "+v"(l), "+v"(m), "+v"(mb));
-        {
-            constexpr int NS = 2 * RT * DT, PF = D == 128 ? 3 : 2;
+        // O += P V over the sub-tiles [R0, R0 + ST)
+        auto product = [&](auto r0_tag) __attribute__((always_inline)) {
+            constexpr int C0 = 2 * decltype(r0_tag)::value, NS = 2 * ST * DT, PF = D == 128 ? 3 : 2;
             s16x4 va4[NS], vb4[NS];
             auto load = [&](auto si) __attribute__((always_inline)) {
-                constexpr int s = decltype(si)::value, cc = s / DT, dt = s % DT;
+                constexpr int s = decltype(si)::value, cc = C0 + s / DT, dt = s % DT;
                 va4[s] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                     (lds_s16x4_t*)(uintptr_t)(vad[2 * dt] + (uint32_t)(OFF + 16 * cc * ROWB)));
                 vb4[s] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -1731,7 +1690,7 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
             };
             static_for<PF>(load);
             static_for<NS>([&](auto si) __attribute__((always_inline)) {
-                constexpr int s = decltype(si)::value, cc = s / DT, dt = s % DT;
+                constexpr int s = decltype(si)::value, cc = C0 + s / DT, dt = s % DT;
                 if constexpr (s + PF < NS) load(std::integral_constant<int, s + PF>{});
                 const s16x8 v8 = {va4[s][0], va4[s][1], va4[s][2], va4[s][3],
                                   vb4[s][0], vb4[s][1], vb4[s][2], vb4[s][3]};
@@ -1739,7 +1698,62 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
                                                                    0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             });
-        }
+        };
+        // the softmax step of attn_fwd_kernel over the sub-tiles [R0, R0 + ST):
+        // the running max is kept while no lane's probabilities of the step
+        // sum past kSumLimit
+        auto step = [&](auto r0_tag) __attribute__((always_inline)) {
+            constexpr int R0 = decltype(r0_tag)::value;
+            float ps0, ps1;
+            auto exps = [&]() __attribute__((always_inline)) {
+                ps0 = 0.0f;
+                ps1 = 0.0f;
+#pragma unroll
+                for (int qq = 0; qq < ST * 16; ++qq) {
+                    const int rt = R0 + qq / 16, c1 = (qq / 8) % 2, e = qq % 8;
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[rt][8 * c1 + e], c2, -mb));
+                    pb[2 * rt + c1][e] = static_cast<__bf16>(p);
+                    if (qq % 2 == 0)
+                        ps0 += p;
+                    else
+                        ps1 += p;
+                    if (qq % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int c = 2 * R0; c < 2 * (R0 + ST); ++c) asm volatile("" : "+v"(pb[c]));
+            };
+            bool fast = __all(m > -INFINITY);
+            if (fast) {
+                exps();
+                fast = !__any(!(ps0 + ps1 <= kSumLimit));
+            }
+            if (!fast) {
+                asm volatile("" ::: "memory");
+                float mx = -INFINITY;
+#pragma unroll
+                for (int rt = R0; rt < R0 + ST; ++rt)
+#pragma unroll
+                    for (int ii = 0; ii < 16; ii += 2) mx = fmaxf(mx, fmaxf(sacc[rt][ii], sacc[rt][ii + 1]));
+                mx = max_across_halves(mx);
+                const float m_new = fmaxf(m, mx);
+                const float alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * c2);
+                if (__any(alpha != 1.0f)) {
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
+                    l *= alpha;
+                }
+                m = m_new;
+                mb = m_new == -INFINITY ? 0.0f : m_new * c2;
+                exps();
+            }
+            l += ps0 + ps1;
+            asm volatile("" : "+v"(l), "+v"(m), "+v"(mb));
+        };
+        static_for<RT / ST>([&](auto si) __attribute__((always_inline)) {
+            constexpr int R0 = decltype(si)::value * ST;
+            step(std::integral_constant<int, R0>{});
+            product(std::integral_constant<int, R0>{});
+        });
     };
 
 #pragma unroll

@@ -87,6 +87,44 @@ def test_attention_narrow_tiles_edges(d, bs, tail):
     _check_rows(host, [pick], o, lse, d, bs, L, [(0, h) for h in range(H)], list(range(n)))
 
 
+@pytest.mark.parametrize("d,bs", [(128, 128), (128, 64), (64, 128), (64, 64)])
+def test_attention_row_does_not_depend_on_the_other_row_of_its_pair(d, bs):
+    """A query block's output is the same, bit for bit, whether the other block
+    of its pair keeps the same list (every tile in the shared part of the
+    walk) or none (every tile in its own part): the softmax steps cover the
+    same kv rows in both.  Scores wide enough that the running max moves in the
+    middle of a tile, a short tail block."""
+    n, H = 13, 2
+    L = (n - 1) * bs + bs // 2 + 3
+    _, (q, k, v) = _layer(1, H, L, d, 300 + d + bs, spread=2.5)
+    rng = np.random.default_rng(d + bs)
+    shape = M.make_shape(1, H, L, d, bs)
+    lists = [[np.sort(rng.choice(n, size=int(rng.integers(1, n + 1)), replace=False)) for _ in range((n + 1) // 2)]
+             for _ in range(H)]
+
+    def run(keeps):
+        idx = torch.zeros((1, H, n, n), dtype=torch.int32)
+        cnt = torch.zeros((1, H, n), dtype=torch.int32)
+        for h in range(H):
+            for i in range(n):
+                if keeps(i):
+                    js = lists[h][i // 2]
+                    cnt[0, h, i] = len(js)
+                    idx[0, h, i, :len(js)] = torch.from_numpy(js)
+        o = torch.empty_like(q)
+        lse = torch.empty((1, H, L), dtype=torch.float32, device="cuda")
+        M.mod_block_sparse_attn_fwd(shape, q, k, v, idx.cuda(), cnt.cuda(), 0.0, o, lse)
+        return o.view(torch.int16), lse
+
+    o_both, lse_both = run(lambda i: True)
+    for side in (0, 1):
+        o, lse = run(lambda i: i % 2 == side)
+        for i in range(side, n, 2):
+            rows = slice(i * bs, min(L, (i + 1) * bs))
+            assert torch.equal(lse[:, :, rows], lse_both[:, :, rows]), (side, i)
+            assert torch.equal(o[:, :, rows], o_both[:, :, rows]), (side, i)
+
+
 @pytest.mark.parametrize("d,bs,n", [(128, 128, 101), (64, 64, 64), (128, 64, 33)])
 def test_attention_plan_without_counts(d, bs, n):
     """Fewer items than resident groups and no slots (short sequences, or a
