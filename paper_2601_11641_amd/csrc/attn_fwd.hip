@@ -274,7 +274,7 @@ struct Plan {
     int* ctr;           // fetch counters, ctr[kCtrStride * x] for XCD x
     int* len;           // [8] items per XCD list
     int* start;         // [8] first item of each XCD list in `items`
-    int* misc;          // [0] split pairs, [1] chunk length in steps (0: none)
+    int* misc;          // [0] split pairs, [1] chunk length in steps (0: none), [2] items
     long long* headpre; // [8][BH + 1] per work-group: cost before each head's first pair
     int* items;         // [BH * npairs + S]
     int4* chunks;       // [S] chunk items: {pair, first step, end step, 0}
@@ -609,6 +609,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         if (x == 0) {
             pl.misc[0] = nsplit;
             pl.misc[1] = cs;
+            int all = 0;
+            for (int xx = 0; xx < kXcds; ++xx) all += xcnt[xx];
+            pl.misc[2] = all;
         }
     }
     // Longest items first: a bucket sort of the list by decreasing cost, in
@@ -1537,6 +1540,15 @@ __global__ __launch_bounds__(BS * 4, (kNarrowWaves<D, BS>)) void attn_narrow_ker
     int* const item_s = wsum + 2 * NT / 64;
     static_assert(TILE >= kMaxBlocks + 256, "the union build's scratch must fit one tile buffer");
     static_assert(TILE / 1024 == NV * 2 * QW, "each wave copies one swizzle period of a tile");
+
+    // A launch may have fewer items than resident groups (few pairs, and a plan
+    // that splits few of them).  Then only the first groups take part: the
+    // chip spreads those over its units, while any group may be the first to
+    // fetch, which left some units with two or more items and others with none
+    // (d = 64, 128-token blocks, 2 heads of 150, 30% kept: 126 us with one group
+    // per unit, 174 with all fetching, 117 so).
+    if constexpr (!DIRECT)
+        if (BH * ((n + 1) / 2) < (int)gridDim.x && (int)blockIdx.x >= Plan(ws, BH, (n + 1) / 2, S).misc[2]) return;
 
     for (;;) {
     int tid = threadIdx.x;

@@ -63,6 +63,34 @@ def test_attention_more_items_than_resident_groups(d, bs, tail):
         _check_rows(host, rows, o, lse, d, bs, L, [(0, 0), (0, 8), (1, 4)], [0, 1, 2, 49, 50, 98, 99, 100])
 
 
+@pytest.mark.parametrize("d,bs,H,n", [(64, 128, 2, 150), (128, 64, 3, 99), (64, 64, 2, 230)])
+def test_attention_fewer_items_than_resident_groups(d, bs, H, n):
+    """Planned launches whose items, split or not, leave resident groups
+    without one: those leave at once (the plan counts the items), the others
+    do all of them."""
+    L = (n - 1) * bs + 9
+    host, (q, k, v) = _layer(1, H, L, d, n + bs)
+    rng = np.random.default_rng(n)
+    shape = M.make_shape(1, H, L, d, bs)
+    pairs = H * ((n + 1) // 2)
+    size = M.mod_attn_workspace_bytes(shape)
+    for keep in (n // 4, n):
+        rows = [[np.sort(rng.choice(n, size=keep, replace=False)).tolist() for _ in range(n)] for _ in range(H)]
+        idx = torch.zeros((1, H, n, n), dtype=torch.int32)
+        idx[0, :, :, :keep] = torch.tensor(rows, dtype=torch.int32)
+        cnt = torch.full((1, H, n), keep, dtype=torch.int32, device="cuda")
+        ws = torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda")
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((1, H, L), float("nan"), dtype=torch.float32, device="cuda")
+        M.mod_block_sparse_attn_fwd(shape, q, k, v, idx.cuda(), cnt, 0.0, o, lse, ws, size)
+        head = ws[:4 * (PLAN_MISC_INT + 3)].view(torch.int32).cpu().tolist()
+        lens, (splits, steps, items) = head[PLAN_MISC_INT - 16:PLAN_MISC_INT - 8], head[PLAN_MISC_INT:]
+        assert items == sum(lens) and (splits > 0) == (keep == n), (lens, splits, steps, items)
+        assert (items == pairs) if splits == 0 else (pairs < items), (items, pairs)
+        assert not torch.isnan(o.float()).any() and not torch.isnan(lse).any()
+        _check_rows(host, [rows], o, lse, d, bs, L, [(0, 0), (0, H - 1)], [0, 1, n // 2, n - 2, n - 1])
+
+
 @pytest.mark.parametrize("d,bs,tail", [(128, 64, 1), (64, 128, 65), (64, 128, 64), (64, 64, 33)])
 def test_attention_narrow_tiles_edges(d, bs, tail):
     """Walks of zero, one and two tiles in either part, and a short tail block
