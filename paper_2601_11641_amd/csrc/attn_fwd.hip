@@ -2126,21 +2126,49 @@ __global__ __launch_bounds__(BS * 4, 1) void stat_count_kernel(
     if (g == 1 && qw == 0 && ucnt > 0 && ((em2 >> 17) & 1u) != 0) flush(1, (ucnt - 1) & 1, (int)(em2 & 0xFFFF));
 }
 
+// Work-groups of the count kernel resident on a compute unit at once: its
+// registers and LDS (86, 53 or 37 KB) allow one with 128-row blocks, three at
+// 128 x 64 and four at 64 x 64.
+template <int D, int BS>
+constexpr int kCountGroupsPerCu = BS == 128 ? 1 : (D == 128 ? 3 : 4);
+
+// Parts that every walk of the count is cut into (every listed block is
+// counted by itself, so a walk may be cut anywhere).  `groups` whole walks run
+// in rounds of `resident` work-groups; c parts of each make more, shorter
+// rounds, which fill an idle chip or a last round that few walks fill, and
+// cost a start (lists, union, Q) of about four tiles' time per round: of the
+// powers of two that leave eight blocks per part, the one whose rounds end
+// first.  The list lengths are not known here: the walk is taken to have an
+// eighth of the blocks, since a cut that wins there wins on longer lists too
+// (its rounds hold less of the walk), while one chosen for full lists loses on
+// short ones.  Whole update of the statistic, uncut, with this rule, and with
+// parts until there are 16 groups per unit: d = 128, block 128, 3 heads of 929
+// blocks, full lists 9.19, 8.31, 8.28 ms, 5% kept 769, 758, 813 us; 24 heads
+// of 200 (the rule cuts nothing), 10% kept 404, 441 us, full lists 3.11, 2.96
+// ms; 24 heads of 64 (nor here), full 315, 344 us, 10% kept 58, 112 us; one
+// head of 64 95, 27, 35 us; block 64, 8 heads of 64 71, 48, 58 us.
+constexpr int count_parts(long groups, int n, long resident) {
+    constexpr int kStart = 4, kMinBlocks = 8;
+    // the launch's time in 8192ths of a tile's
+    auto cost = [=](long c) { return ((groups * c + resident - 1) / resident) * (kStart * 8 * 1024 + n * 1024L / c); };
+    int best = 1;
+    for (int c = 2; n / c >= kMinBlocks; c *= 2)
+        if (cost(c) <= cost(best)) best = c;
+    return best;
+}
+static_assert(count_parts(32, 64, 256) == 8, "a part of the chip: cut until it is full");
+static_assert(count_parts(8 * 32, 64, 256) == 1 && count_parts(24 * 32, 64, 256) == 1, "whole rounds: uncut");
+static_assert(count_parts(2 * 100, 200, 256) == 1 && count_parts(24 * 100, 200, 256) == 1, "nothing to gain: uncut");
+static_assert(count_parts(3 * 465, 929, 256) == 2, "half of a nearly empty last round");
+static_assert(count_parts(8 * 32, 64, 768) == 2 && count_parts(32 * 32, 64, 768) == 2, "several groups per unit");
+
 template <int D, int BS>
 hipError_t launch_count(const uint16_t* q, const uint16_t* k, const int32_t* kv_idx, const int32_t* kv_cnt,
                         const float* lse, float scale, float log_eta, double* stat, int BH, int L, int n,
                         int nv, hipStream_t s) {
     const unsigned npv = (unsigned)(nv + 1) / 2;
-    // Every listed block is counted by itself, so a walk may be cut anywhere:
-    // into a power of two of parts of at least 16 blocks, until there are 16
-    // work-groups per compute unit, which leaves a last round of a few percent
-    // (3 heads of 929 blocks, dense: 1395 whole walks took six rounds of 256
-    // units for 5.4 rounds of work, 8.77 ms; 8.23 with four parts of each).  The
-    // parts of a pair are neighbouring work-groups, so an XCD sees the same
-    // part of every walk and keeps its K tiles (three parts: 8.68 ms).
-    const long groups = (long)BH * npv, want = 16L * persistent_groups();
-    int chunks = 1;
-    while (groups * chunks < want && n / (2 * chunks) >= 16) chunks *= 2;
+    const long groups = (long)BH * npv;
+    const int chunks = count_parts(groups, n, (long)persistent_groups() * kCountGroupsPerCu<D, BS>);
     hipLaunchKernelGGL((stat_count_kernel<D, BS>), dim3((unsigned)(groups * chunks)), dim3(BS * 4), 0, s, q, k,
                        kv_idx, kv_cnt, lse, scale, log_eta, stat, L, n, nv, chunks);
     return hipGetLastError();

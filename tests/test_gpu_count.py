@@ -22,8 +22,8 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 
-@pytest.mark.parametrize("d,bs,n,text", [(128, 128, 31, 0), (64, 64, 33, 0), (128, 64, 67, 0), (64, 128, 71, 300),
-                                         (128, 128, 65, 100)])
+@pytest.mark.parametrize("d,bs,n,text", [(128, 128, 15, 0), (128, 128, 31, 0), (64, 64, 33, 0), (128, 64, 67, 0),
+                                         (64, 128, 71, 300), (128, 128, 65, 100)])
 def test_counts_of_cut_walks(d, bs, n, text):
     H, eta = 2, 3e-3
     T = (n * bs - text - 23) // 2
