@@ -815,10 +815,12 @@ __global__ void gate_kernel(const double* __restrict__ Xa, const double* __restr
 // ---------------------------------------------------------------------------
 // a4 + a5: extrapolation and per-row selection in one launch.
 //
-// A work-group of four waves serves 4 rpw consecutive query rows of one head.
-// It extrapolates the diagonals and columns these rows meet into LDS
-// (X2 + (X2 - X1) w, Section 5.2; n + 4 rpw - 1 and n values), writes its
-// share of the prediction, and each wave then selects rpw rows.
+// A work-group of four waves serves consecutive query rows of one head.  It
+// extrapolates the diagonals and columns these rows meet (X2 + (X2 - X1) w,
+// Section 5.2; n + rows - 1 and n values) and writes its share of the
+// prediction.  Up to 2304 blocks each wave then selects rpw rows; beyond, the
+// four waves share a row (SHARED), since a wave's 37 to 64 keys per lane leave
+// one or two waves per SIMD and all of a step's instructions in one chain.
 //
 //   sigma_j = n (c~[j-i] + d~[j]) in fp64, rounded to float: the ranking key.
 //   The non-forced blocks are ranked by (sigma desc, j asc).  TOPK keeps the
@@ -827,21 +829,27 @@ __global__ void gate_kernel(const double* __restrict__ Xa, const double* __restr
 //   row total (fp64 sums; at least one block).  The kept set is compacted in
 //   ascending j.
 // Every free block j holds the order bits of its key (vb, 0 for forced blocks
-// and padding; block lane + 64 e in element e).  The kept free blocks are
-// those whose bits exceed a boundary p, plus the first r in ascending j of
-// those whose bits equal p.  Both budgets ask for the largest threshold at or
-// above which the keys' count (TOPK) or mass (MASS, summed in one fixed order)
-// still reaches the target; that predicate only changes at keys, so any search
-// finds the same set.  A step costs EW compares with a scalar count each
-// (MASS: also EW fp64 additions), so few steps are what counts: the search
-// starts at the boundary of the row before (neighbouring rows shift the
-// diagonals by one), gallops until it has the boundary between two
-// thresholds, halves their distance in order bits, and ends once one key lies
-// between them: 10-12 steps for a first row, 4-6 for the next ones (32 when
-// built bit by bit; interpolating between the counts takes as many).  The
-// ballots that count also place the kept blocks, so the stores of a wave are
-// contiguous.  With the extrapolation: TOPK, 40 heads of 591 blocks 83 -> 44
-// us; MASS, 24 heads of 929 blocks 147 -> 90 us; bound by vector issue.
+// and padding; block first + lane + 64 e in element e, first the wave's).  The
+// kept free blocks are those whose bits exceed a boundary p, plus the first r
+// in ascending j of those whose bits equal p.  Both budgets ask for the largest
+// threshold at or above which the keys' count (TOPK) or mass (MASS, summed in
+// one fixed order) still reaches the target; that predicate only changes at
+// keys, so any search finds the same set.  A step costs EW compares with a
+// scalar count each (MASS: also EW fp64 additions) and some twenty scalar
+// instructions, so few steps are what counts: the search starts at the boundary
+// of the row before (neighbouring rows shift the diagonals by one), gallops
+// until it has the boundary between two thresholds, halves their distance in
+// order bits, and ends once one key lies between them: 10-12 steps for a
+// first row, 4-6 for the next ones (interpolating between the counts takes as
+// many).  The ballots that count also place
+// the kept blocks, so the stores of a wave are contiguous.
+// The lane's block number is made opaque once per row: the lane masks of the
+// range and forced tests, kept across rows, spilled scalar registers from 448
+// (MASS) and 640 (TOPK) blocks on.
+// With the extrapolation: TOPK, 40 heads of 591 blocks 83 -> 41 us; MASS, 24
+// heads of 929 blocks 139 -> 71 us; bound by vector issue.  SHARED, 8 heads of
+// 2600: TOPK 290 -> 147, MASS 485 -> 259 us (a wave per row: 137 and 273); one
+// head of 4096: TOPK 71 -> 60, MASS 113 -> 105 us (82 and 147).
 //
 // With a text segment after the video (token-type-aware masking) n counts
 // the video blocks, the lists have ldn >= n entries per row, the block tb0
@@ -898,14 +906,21 @@ RowGrid row_grid(int BH, int n, int ldn, int tb0) {
     return RowGrid{rpw, chunks, (unsigned)(chunks + std::max(0, ldn - tb0))};
 }
 
-template <int EW, bool MASS>
+constexpr int kWideBlocks = 2304;      // longest row that one wave selects
+constexpr int kMaxSharedRows = 4;      // rows of a work-group whose waves share them
+
+// rpw: rows per wave, or (SHARED) per work-group.
+template <int EW, bool MASS, bool SHARED>
 __global__ __launch_bounds__(kThreads) void select_rows_kernel(
     const double* __restrict__ X1, const double* __restrict__ X2, double w, double* __restrict__ pred,
     const int32_t* __restrict__ gate, const int* __restrict__ row_lo, const int* __restrict__ row_hi, int topk,
     double tau, int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, int n, int F, int ldn, int tb0,
     int rpw, int chunks) {
-    __shared__ double cs[64 * EW + kWavesPerGroup * kMaxRowsPerWave];   // diagonals c0 ..
-    __shared__ double ds[64 * EW];                                      // columns
+    constexpr int NW = kWavesPerGroup, WPR = SHARED ? NW : 1;                       // waves per row
+    __shared__ double cs[64 * EW * WPR + (SHARED ? kMaxSharedRows : NW * kMaxRowsPerWave)];   // diagonals c0 ..
+    __shared__ double ds[SHARED ? 1 : 64 * EW];                                     // columns
+    __shared__ int xi[2][NW];       // SHARED: the waves' parts of a count and of a mass,
+    __shared__ double xd[2][NW];    // two sets in turn (one barrier per exchange)
     const int bh = blockIdx.y;
     if ((int)blockIdx.x >= chunks) {
         keep_all(kv_idx, kv_cnt, (size_t)bh * ldn + tb0 + (blockIdx.x - chunks), ldn);
@@ -913,25 +928,68 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(
     }
     const int m = 3 * n - 1;
     const size_t xo = (size_t)bh * (m + F);
-    const int i0 = blockIdx.x * kWavesPerGroup * rpw;
-    const int i1 = min(n, i0 + kWavesPerGroup * rpw);    // rows [i0, i1)
+    const int rows = SHARED ? rpw : NW * rpw;
+    const int i0 = blockIdx.x * rows;
+    const int i1 = min(n, i0 + rows);                    // rows [i0, i1)
     const int c0 = n - i1;                               // diagonal index of (i1 - 1, 0)
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int jw = (SHARED ? wv * 64 * EW : 0) + lane;   // this lane's first block
     for (int a = threadIdx.x; a < n + (i1 - i0) - 1; a += kThreads) cs[a] = extrapolated(X1, X2, w, xo + c0 + a);
-    for (int a = threadIdx.x; a < n; a += kThreads) ds[a] = extrapolated(X1, X2, w, xo + 2 * n - 1 + a);
+    double dr[SHARED ? EW : 1];     // SHARED: the lane's columns stay in registers, which halves the LDS
+    if constexpr (SHARED) {
+#pragma unroll
+        for (int e = 0; e < EW; ++e) dr[e] = extrapolated(X1, X2, w, xo + 2 * n - 1 + min(jw + 64 * e, n - 1));
+    } else {
+        for (int a = threadIdx.x; a < n; a += kThreads) ds[a] = extrapolated(X1, X2, w, xo + 2 * n - 1 + a);
+    }
     {
         const int per = (m + chunks - 1) / chunks, a1 = min(m, ((int)blockIdx.x + 1) * per);
         for (int a = blockIdx.x * per + threadIdx.x; a < a1; a += kThreads)
             pred[(size_t)bh * m + a] = extrapolated(X1, X2, w, xo + a);
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool g = gate[bh] != 0;
+    int par = 0;
+    // SHARED: a wave's count and mass summed over the waves, in wave order
+    auto exchange = [&](int& c, double& s) {
+        if constexpr (SHARED) {
+            if (lane == 0) {
+                xi[par][wv] = c;
+                if constexpr (MASS) xd[par][wv] = s;
+            }
+            __syncthreads();
+            c = 0;
+            s = 0.0;
+#pragma unroll
+            for (int x = 0; x < NW; ++x) {
+                c += xi[par][x];
+                if constexpr (MASS) s += xd[par][x];
+            }
+            par ^= 1;
+        }
+    };
+    // SHARED: the counts of the waves before this one, and of all
+    auto before = [&](int c, int& all) {
+        if (lane == 0) xi[par][wv] = c;
+        __syncthreads();
+        int pre = 0;
+        all = 0;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) {
+            pre += x < wv ? xi[par][x] : 0;
+            all += xi[par][x];
+        }
+        par ^= 1;
+        return pre;
+    };
     uint32_t guess = 0xBF800000u;    // 1.0: the score of every block of a uniform map
     uint32_t stride = 1u << 23;      // first gallop step: a factor of two
     for (int rr = 0; rr < rpw; ++rr) {
-        const int i = i0 + wv * rpw + rr;
+        const int i = i0 + (SHARED ? 0 : wv * rpw) + rr;
         if (i >= min(i1, tb0)) break;
+        int jl = jw;
+        asm volatile("" : "+v"(jl));    // no lane mask is kept from one row to the next
         const int flo = row_lo[i], fhi = row_hi[i];
         // forced: the frame blocks of i (gate on) and the block shared by the
         // video and the text segment (tb0 < n), which is a text block
@@ -943,43 +1001,59 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(
 
         double forced_mass = 0.0;
         uint32_t vb[EW];
-        float ms[EW];    // positive mass of a free key
+        float ms[SHARED ? 1 : EW];    // positive mass of a free key
 #pragma unroll
         for (int e = 0; e < EW; ++e) {
-            const int j = lane + 64 * e;
+            const int j = jl + 64 * e;
             vb[e] = 0;
-            ms[e] = 0.0f;
+            if constexpr (!SHARED) ms[e] = 0.0f;
             if (j < n) {
-                const double sv = static_cast<double>(n) * (cs[j + (i1 - 1 - i)] + ds[j]);
+                double dj;
+                if constexpr (SHARED) dj = dr[e];
+                else dj = ds[j];
+                const double sv = static_cast<double>(n) * (cs[j + (i1 - 1 - i)] + dj);
                 const float kf = static_cast<float>(sv);
                 if (is_forced(j)) {
                     if constexpr (MASS) forced_mass += fmax(static_cast<double>(kf), 0.0);
                 } else {
                     vb[e] = order_bits(kf);
-                    ms[e] = fmaxf(kf, 0.0f);
+                    if constexpr (!SHARED) ms[e] = fmaxf(kf, 0.0f);
                 }
             }
         }
-        auto count_ge = [&](uint32_t th) {   // free keys with bits >= th (th >= 1)
-            int cnt = 0;
-#pragma unroll
-            for (int e = 0; e < EW; ++e) cnt += __popcll(__ballot(vb[e] >= th));
-            return cnt;
-        };
-        auto mass_ge = [&](uint32_t th) {    // their mass (th >= 1)
+        // the free keys with bits >= th (th >= 1), and (MASS) their mass, in
+        // one pass so that no compare's mask outlives its element
+        auto at_least = [&](uint32_t th, double& mass) {
+            int c = 0;
             double s = 0.0;
 #pragma unroll
-            for (int e = 0; e < EW; ++e) s += static_cast<double>(vb[e] >= th ? ms[e] : 0.0f);
-            return wave_total_f64(s);
+            for (int e = 0; e < EW; ++e) {
+                if constexpr (MASS && SHARED) asm volatile("" : "+v"(vb[e]));   // (the mass is not kept beside the bits)
+                const bool ge = vb[e] >= th;
+                c += __popcll(__ballot(ge));
+                if constexpr (MASS) {
+                    float me;    // positive keys have the sign bit set in their order bits
+                    if constexpr (SHARED) me = fmaxf(__uint_as_float(vb[e] ^ 0x80000000u), 0.0f);
+                    else me = ms[e];
+                    s += static_cast<double>(ge ? me : 0.0f);
+                }
+            }
+            if constexpr (MASS) s = wave_total_f64(s);
+            exchange(c, s);
+            mass = s;
+            return c;
         };
 
         uint32_t p = 0;      // boundary bits
         int r = 0;           // keys kept at the boundary, in ascending j
         int keep = -1;       // free keys kept when all or none are
-        double fm = 0.0, target = 0.0;
+        double fm = 0.0, target = 0.0, mass = 0.0;
         if constexpr (MASS) {
             fm = wave_total_f64(forced_mass);
-            const double total = fm + (n_free > 0 ? mass_ge(1u) : 0.0);
+            int none = 0;
+            exchange(none, fm);
+            (void)at_least(1u, mass);
+            const double total = fm + (n_free > 0 ? mass : 0.0);
             target = tau * total;
             if (fm >= target)
                 keep = min(n_free, nf > 0 ? 0 : 1);
@@ -1003,8 +1077,8 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(
             uint32_t delta = stride, th = guess;
             while (c_lo - c_hi > 1 && hi - lo > 1) {
                 th = min(max(th, lo + 1), hi - 1);
-                const int c = count_ge(th);
-                if (by_mass ? fm + mass_ge(th) >= target : c >= keep) {
+                const int c = at_least(th, mass);
+                if (by_mass ? fm + mass >= target : c >= keep) {
                     lo = th;
                     c_lo = c;
                     have_lo = true;
@@ -1029,8 +1103,9 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(
                 p = lo;
                 if (by_mass) {
                     // the fewest of the equal keys at p that reach the target
-                    const double above = fm + mass_ge(p + 1);
-                    const int ties = count_ge(p) - count_ge(p + 1);
+                    const int c1 = at_least(p + 1, mass);
+                    const double above = fm + mass;
+                    const int ties = at_least(p, mass) - c1;
                     const double mp = fmax(static_cast<double>(order_bits_to_float(p)), 0.0);
                     r = 1;
                     while (r < ties && above + static_cast<double>(r) * mp < target) ++r;
@@ -1040,28 +1115,57 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(
             }
         }
 
-        // compaction in ascending j: block lane + 64 e, element by element
+        // compaction in ascending j: element by element, block jl + 64 e
         // (the forced test is evaluated again rather than kept as EW lane masks)
         asm volatile("" : "+s"(f0), "+s"(f1), "+s"(f2));
         const size_t orow = (size_t)bh * ldn + i;     // row of the [BH, ldn, ldn] lists
         int32_t* out = kv_idx + orow * ldn;
         int pos = 0, ties = 0;
-#pragma unroll
-        for (int e = 0; e < EW; ++e) {
-            const int j = lane + 64 * e;
-            bool kept = vb[e] > p || is_forced(j);
+        auto is_kept = [&](int e) {    // elements in order
+            bool kept = vb[e] > p || is_forced(jl + 64 * e);
             if (r > 0) {
                 const bool eq = vb[e] == p;
                 const uint64_t me = __ballot(eq);
                 kept = kept || (eq && ties + mask_rank(me) < r);
                 ties += __popcll(me);
             }
+            return kept;
+        };
+        auto put = [&](bool kept, int e) {
             const uint64_t mk = __ballot(kept);
-            if (kept) out[pos + mask_rank(mk)] = j;
+            if (kept) out[pos + mask_rank(mk)] = jl + 64 * e;
             pos += __popcll(mk);
+        };
+        int total, tid = lane, step = 64;
+        if constexpr (SHARED) {
+            // the waves hold consecutive blocks: the keys at the boundary, then
+            // the kept blocks, of the waves before this one
+            if (r > 0) {
+                int mine = 0;
+#pragma unroll
+                for (int e = 0; e < EW; ++e) mine += __popcll(__ballot(vb[e] == p));
+                ties = before(mine, total);
+            }
+            uint32_t km = 0;    // bit e: this lane's block of element e is kept
+            int mine = 0;
+#pragma unroll
+            for (int e = 0; e < EW; ++e) {
+                const bool kept = is_kept(e);
+                km |= kept ? 1u << e : 0u;
+                mine += __popcll(__ballot(kept));
+            }
+            pos = before(mine, total);
+#pragma unroll
+            for (int e = 0; e < EW; ++e) put((km >> e) & 1u, e);
+            tid = threadIdx.x;
+            step = kThreads;
+        } else {
+#pragma unroll
+            for (int e = 0; e < EW; ++e) put(is_kept(e), e);
+            total = pos;
         }
-        for (int j = n + lane; j < ldn; j += 64) out[pos + (j - n)] = j;
-        if (lane == 0) kv_cnt[orow] = pos + (ldn - n);
+        for (int j = n + tid; j < ldn; j += step) out[total + (j - n)] = j;
+        if (tid == 0) kv_cnt[orow] = total + (ldn - n);
     }
 }
 
@@ -1298,24 +1402,40 @@ hipError_t launch_gate(const double* Xa, const double* Xb, int32_t* gate, int BH
 hipError_t launch_select(const double* X1, const double* X2, double w, double* pred, const int32_t* gate,
                          const int* row_lo, const int* row_hi, int mode, int k, double tau, int32_t* kv_idx,
                          int32_t* kv_cnt, int BH, int n, int F, int ldn, int tb0, hipStream_t s) {
-    const RowGrid rg = row_grid(BH, n, ldn, tb0);
-    auto go = [&](auto ew) {
+    RowGrid rg = row_grid(BH, n, ldn, tb0);
+    auto go = [&](auto ew, auto shared) {
         constexpr int EW = decltype(ew)::value;
-        auto kern = mode == 0 ? select_rows_kernel<EW, false> : select_rows_kernel<EW, true>;
+        constexpr bool SHARED = decltype(shared)::value;
+        auto kern = mode == 0 ? select_rows_kernel<EW, false, SHARED> : select_rows_kernel<EW, true, SHARED>;
         hipLaunchKernelGGL(kern, dim3(rg.groups, (unsigned)BH), dim3(kThreads), 0, s, X1, X2, w, pred, gate, row_lo,
                            row_hi, k, tau, kv_idx, kv_cnt, n, F, ldn, tb0, rg.rpw, rg.chunks);
         return hipGetLastError();
     };
+    hipError_t e = hipErrorInvalidValue;
+    if (n > kWideBlocks) {
+        // rows per work-group: as few as give the chip four groups per unit, so
+        // that the first row's search and the loads are shared (one head of
+        // 4096 blocks, MASS: 106, 105 and 115 us with two, four and eight rows;
+        // 8 of 2600: 287, 259, 264)
+        rg.rpw = (int)std::max<long>(1, std::min<long>(kMaxSharedRows, (long)BH * n / 1024));
+        rg.chunks = (n + rg.rpw - 1) / rg.rpw;
+        rg.groups = (unsigned)(rg.chunks + std::max(0, ldn - tb0));
+        const int ew = (n + 255) / 256;
+        static_for<5, kMaxBlocks / 512 + 1>([&](auto w) {
+            constexpr int EW = 2 * decltype(w)::value;
+            if (ew <= EW && ew > EW - 2) e = go(std::integral_constant<int, EW>{}, std::true_type{});
+        });
+        return e;
+    }
     // the fewest keys per lane that hold a row (a search step costs one
     // compare per key slot): every width up to 1024 blocks, then every fourth
     const int ew = (n + 63) / 64;
-    hipError_t e = hipErrorInvalidValue;
     static_for<1, 17>([&](auto w) {
-        if (ew == decltype(w)::value) e = go(w);
+        if (ew == decltype(w)::value) e = go(w, std::false_type{});
     });
-    static_for<5, kMaxBlocks / 256 + 1>([&](auto w) {
+    static_for<5, kWideBlocks / 256 + 1>([&](auto w) {
         constexpr int EW = 4 * decltype(w)::value;
-        if (ew > 16 && ew <= EW && ew > EW - 4) e = go(std::integral_constant<int, EW>{});
+        if (ew > 16 && ew <= EW && ew > EW - 4) e = go(std::integral_constant<int, EW>{}, std::false_type{});
     });
     return e;
 }

@@ -84,3 +84,29 @@ def test_attention_statistic_fit(name):
         counts = G * sizes[:, None] * sizes[None, :]
         assert np.abs(counts - np.round(counts)).max() <= 1e-9 * bs * bs and G.max() > 0
         _check_fit(st, H, G, regions, heads)
+
+
+@pytest.mark.parametrize("F,T", [(3, 65550), (2, 131060)])
+def test_fit_of_wide_maps(F, T):
+    """3073 and 4096 blocks (the largest): the block mass on sampled rows, and X
+    as the minimum-norm solution of the normal equations -- the residual G - M X
+    sums to zero over every diagonal, column and frame square, and X has no
+    component along the null vector.  An error of 1e-9 of the largest
+    coefficient (as above) in each of a cell's three terms, over n cells."""
+    L, d, bs = F * T, 64, 64
+    n, regions = O.num_blocks(L, bs), O.frame_regions(L, bs, T)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    base = torch.randn((1, 1, F, 1, d), device="cuda", generator=gen)
+    q, k = ((base + torch.randn((1, 1, F, T, d), device="cuda", generator=gen)).reshape(1, 1, L, d).bfloat16()
+            .contiguous() for _ in range(2))
+    with M.Stats(M.make_shape(1, 1, L, d, bs, T), M.make_params(warmup_m=1)) as st:
+        M.mod_collect_stats(st.handle, q, k, 1)
+        G = M.mod_stats_get_block_mass(st.handle, 1, 1, n)[0, 0]
+        X = M.mod_stats_get_anchor(st.handle, 0, 1, 1, st.p)[0][0, 0]
+    qb, kb = (O.pool(bf16_to_f64(x[0, 0]), bs) for x in (q, k))
+    sample = sorted({0, 1, 15, 16, n // 2, n - 2, n - 1, *np.random.default_rng(n).integers(0, n, 24).tolist()})
+    np.testing.assert_allclose(G[sample], O.block_mass(qb[sample], kb, O.block_sizes(L, bs), 1.0 / np.sqrt(d)),
+                               rtol=1e-10, atol=1e-15)
+    bound = 3 * n * 1e-9 * np.abs(X).max()
+    assert np.abs(O.rhs(G - O.reconstruct(X, n, regions), regions)).max() <= bound
+    assert abs(X @ O.null_vector(n, F)) <= bound

@@ -1,10 +1,10 @@
 """GPU parity at the size limits of the kernels, through the C ABI.
 
-* The selection keeps a row's npad = 256 * E keys in registers (E keys per
-  thread, E = 1, 2, 4, 8, 16 by n); the other parity tests reach E = 1
-  (n <= 256) and E = 4 (the 720p layers).  Rows of n = 300, 1172 and 2063
-  blocks (E = 2, 8, 16, each with a short tail block) are checked here
-  against the oracle's predictor, whole layer, both budget modes.
+* The selection keeps a row's keys in the registers of one wave (a width per
+  64 blocks up to 1024, per 256 up to 2304; wider rows are shared by a
+  work-group).  Rows of n = 300, 1172 and 2063 blocks (5, 20 and 36 keys per
+  lane; the latter two with a short tail block) are checked here against the
+  oracle's predictor, whole layer, both budget modes.
 * The attention handles n up to the ABI limit of 4096 blocks (the union
   list of two rows is held in LDS).  A layer of exactly 4096 blocks (short
   tail block) with rows that keep every block, long random lists, and short
@@ -38,11 +38,11 @@ def _layer(name, H, frames, hs, ws, seed):
 
 
 SELECT = {
-    # 3 frames of 80x80: L = 19200, n = 300 (E = 2), no tail
+    # 3 frames of 80x80: L = 19200, n = 300 (5 keys per lane), no tail
     "n300": _layer("n300", 2, 3, 80, 80, 21),
-    # 3 frames of 125x200: L = 75000, n = 1172 (E = 8), tail 56
+    # 3 frames of 125x200: L = 75000, n = 1172 (20 keys per lane), tail 56
     "n1172": _layer("n1172", 1, 3, 125, 200, 22),
-    # 3 frames of 200x220: L = 132000, n = 2063 (E = 16), tail 32
+    # 3 frames of 200x220: L = 132000, n = 2063 (36 keys per lane), tail 32
     "n2063": _layer("n2063", 1, 3, 200, 220, 23),
 }
 
@@ -62,7 +62,7 @@ def test_select_register_widths(name, budget):
 @pytest.mark.parametrize("budget", [("topk", 0.2), ("mass", 0.7)])
 @pytest.mark.parametrize("tau_e", [-1.0, 1.0])
 def test_select_tied_scores_work_group(budget, tau_e):
-    """The one-work-group-per-row selection (n > 1024) on tied scores: every Q
+    """The selection of rows wider than 1024 blocks on tied scores: every Q
     token and every K token the same vector, so a row's scores take one or
     two float32 values and the lists rest on the tie rule (ascending j), the
     frame blocks forced (tau_e below the zero frame energy) or not."""
