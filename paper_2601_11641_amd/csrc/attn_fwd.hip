@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         // start), and keep the best (one head of 195 blocks, 90% kept: 98
         // walks of 176 steps, in three parts two rounds of 59 steps, in two
         // parts one of 88: 377 -> 305 us; the comparison costs 5 us).
-        if (cs == kMinChunkSteps && P <= 4096) {
+        if (cs == kMinChunkSteps && P <= 4096 && W < (Acc)(1 << 20)) {
             constexpr int NC = 5;   // candidate 0: as above; x > 0: the longest walk in x parts
             __shared__ int most, sums[NC];
             if (t == 0) most = 0;
@@ -466,9 +466,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
             __syncthreads();
             const int walk = most;
             // tot: long items, and chunks from bit 16.  Candidate 0's chunks are
-            // at most the steps of the launch / 64 and one more per pair, and
-            // its load per group, under 8 x 64, leaves under 2^18 steps; the
-            // others' are at most 4 per pair: neither half overflows.
+            // at most W / 64 and one more per pair, under 20,481 (W is under
+            // 520 costs per group here, 532,480 with 1024 groups); the others'
+            // are at most 4 per pair, 16,384: neither half overflows.
             int csx[NC], len[NC], tot[NC] = {};
 #pragma unroll
             for (int x = 0; x < NC; ++x) {
