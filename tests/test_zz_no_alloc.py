@@ -1,9 +1,11 @@
 """The no-allocation attention entry point against the one with a caller
 workspace, through the C ABI: identical outputs on two calls in a row (the
 second on a smaller layer, so the library's array holds the first call's
-plan when the second starts), both within the oracle's tolerance on
-sampled query blocks, and shapes whose plan would not fit rejected on the
-host before anything is enqueued."""
+plan when the second starts; both with more pairs of query blocks than
+work-groups fit the chip, which need a plan), the same on layers of fewer
+pairs, which need none, both within the oracle's tolerance on sampled query
+blocks, and shapes whose plan would not fit rejected on the host before
+anything is enqueued."""
 import math
 
 import numpy as np
@@ -65,6 +67,24 @@ def _both(cfg, host, dev, seed, density):
             mx, mean = attention_errors(og[b, h, sl], Oo[sl])
             assert mx <= MAX_ABS and mean <= MEAN_ABS, (b, h, i, mx, mean)
             assert np.abs(lg[b, h, sl] - Lo[sl]).max() <= LSE_ABS
+
+
+def _planned(name, H, d, block, seed):
+    """63 or 64 blocks per head: no walk is split."""
+    return W.LayerConfig(name=name, B=1, H=H, d=d, frames=2, hs=32, ws=block - 1, block=block, seed=seed)
+
+
+# resident groups of the form: 256, 512, 512, 1024
+@pytest.mark.parametrize("first,second", [((64, 64, 40), (128, 128, 9)), ((64, 128, 20), (128, 64, 17)),
+                                          ((128, 128, 16), (64, 64, 33))])
+def test_noalloc_plans_in_the_library_array(first, second):
+    groups = {(128, 128): 256, (64, 128): 512, (128, 64): 512, (64, 64): 1024}
+    for call, (d, block, H) in enumerate((first, second)):
+        cfg = _planned(f"planned{call}", H, d, block, 90 + call)
+        assert cfg.n <= 64 and H * ((cfg.n + 1) // 2) > groups[d, block]
+        print(f"no-alloc call {call + 1}: H={H} L={cfg.L} d={d} block={block}", flush=True)
+        host = W.generate(cfg)
+        _both(cfg, host, tuple(bf16_tensor(x) for x in host), seed=73 + call, density=0.3)
 
 
 def test_noalloc_matches_workspace_entry_on_two_calls():
