@@ -49,7 +49,8 @@ def _check_rows(host, rows, o, lse, d, bs, L, heads, sample):
 
 @pytest.mark.parametrize("d,bs,tail", [(128, 128, 1), (128, 64, 63), (64, 128, 37), (64, 64, 16)])
 def test_attention_more_items_than_resident_groups(d, bs, tail):
-    B, H, n = 2, 9, 101       # 18 heads x 51 pairs, the last of one block
+    # 18 heads x 51 pairs, the last of one block (22 heads where 1024 groups are resident)
+    B, H, n = 2, 11 if d == bs == 64 else 9, 101
     L = (n - 1) * bs + tail
     host, (q, k, v) = _layer(B, H, L, d, 100 + d + bs)
     rows, idx, cnt = _uneven_lists(B, H, n, 7)
@@ -173,27 +174,35 @@ def test_attention_plan_without_counts(d, bs, n):
 
 
 def test_attention_plan_of_sums_beyond_32_bits():
-    """512 heads of 2048 blocks: the plan's sums over all pairs need 64 bits.
-    Every row keeps its own block, the next one and a few full rows all."""
+    """512 heads of 2048 blocks, every count 2048: the plan's sums over all
+    pairs need 64 bits.  Every row lists its own block, the next one and a few
+    rows all; the other slots hold -1, which the attention skips."""
     H, n, d, bs = 512, 2048, 64, 64
     L = n * bs
-    assert H * (n // 2) * (4 + 2 * n) >= 2**31
+    cost = H * (n // 2) * (4 + 2 * n)
+    assert cost >= 2**31
     host, small = _layer(1, 1, L, d, 3)
     q, k, v = (x.expand(1, H, L, d).contiguous() for x in small)
     own = torch.arange(n, dtype=torch.int32)
     row = torch.stack([own, (own + 1) % n], 1).sort(1).values.cuda()
-    idx = torch.zeros((1, H, n, n), dtype=torch.int32, device="cuda")
+    idx = torch.full((1, H, n, n), -1, dtype=torch.int32, device="cuda")
     idx[..., :2] = row
-    cnt = torch.full((1, H, n), 2, dtype=torch.int32, device="cuda")
+    cnt = torch.full((1, H, n), n, dtype=torch.int32, device="cuda")
     full = [0, 777, n - 1]
     for i in full:
         idx[:, :, i] = own.cuda()
-        cnt[:, :, i] = n
     o = torch.empty_like(q)
     lse = torch.empty((1, H, L), dtype=torch.float32, device="cuda")
     shape = M.make_shape(1, H, L, d, bs)
-    ws = torch.empty(M.mod_attn_plan_bytes(shape), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(M.mod_attn_plan_bytes(shape), dtype=torch.uint8, device="cuda")
     M.mod_block_sparse_attn_fwd(shape, q, k, v, idx, cnt, 0.0, o, lse, ws, ws.numel())
+    # the cost before each head and in all, and every pair in exactly one list
+    at = 4 * (PLAN_MISC_INT + 16)
+    before = ws[at:at + 8 * (H + 1)].view(torch.int64).cpu()
+    assert torch.equal(before, torch.arange(H + 1) * (cost // H)) and int(before[-1]) == cost
+    at += 8 * 8 * (H + 1)
+    items = ws[at:at + 4 * H * (n // 2)].view(torch.int32)
+    assert torch.equal(items.sort().values, torch.arange(H * (n // 2), dtype=torch.int32, device="cuda"))
     rows = [[list(range(n)) if i in full else sorted({i, (i + 1) % n}) for i in range(n)]]
     for h in (0, 200, H - 1):
         _check_rows(host, [rows], o[:, h:h + 1], lse[:, h:h + 1], d, bs, L, [(0, 0)], [0, 1, 776, 777, 1500, n - 1])
