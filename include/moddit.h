@@ -131,8 +131,9 @@ int mod_num_coeffs(const mod_shape* shape);
  * closed-form normal matrix of the MOD least-squares problem (Appendix B.4)
  * reduced to its Schur complement, factors and inverts it once, allocates
  * the device buffers and uploads the tables.  Synchronous.  On success *out
- * owns about (2*B*H*n*d + 1.125*B*H*n*n + 8*B*H*n) * 8 bytes of device memory
- * (up to 1.5*B*H*n*n for maps of fewer than 16384 rows in all). */
+ * owns about B*H * (2*n*d + n*n + 29*n) * 8 bytes of device memory, and with
+ * more than 128 blocks or frames another 0.125*B*H*n*n * 8 (up to 0.5 for maps
+ * of fewer than 16384 rows in all). */
 mod_status mod_stats_create(const mod_shape* shape, const mod_params* params,
                             mod_stats** out);
 

@@ -342,7 +342,7 @@ mod_status mod_stats_create(const mod_shape* shape, const mod_params* params, mo
         {(void**)&s->qbar, BH * n * shape->d * sizeof(double)},
         {(void**)&s->kbar, BH * n * shape->d * sizeof(double)},
         {(void**)&s->G, BH * n * n * sizeof(double)},
-        {(void**)&s->part, moddit::fit_part_doubles(s->BH, n) * sizeof(double)},
+        {(void**)&s->part, moddit::fit_part_doubles(s->BH, n, F) * sizeof(double)},
         {(void**)&s->r, BH * s->p * sizeof(double)},
         {(void**)&s->bU, BH * s->q * sizeof(double)},
         {(void**)&s->u, (size_t)moddit::kSolveSplit * BH * s->q * sizeof(double)},   // per-chunk partial products
@@ -357,6 +357,7 @@ mod_status mod_stats_create(const mod_shape* shape, const mod_params* params, mo
         {(void**)&s->chosen, BH * (3 * n - 1) * sizeof(uint8_t)},
     };
     for (auto& a : allocs) {
+        if (a.bytes == 0) continue;
         hipError_t e = hipMalloc(a.p, a.bytes);
         if (e != hipSuccess) {
             free_stats(s);

@@ -27,8 +27,9 @@ hipError_t launch_logits(const double* qbar, const double* kbar, double* G, int 
 // the statistic.  Then its right-hand side M^T vec(G) and the structured
 // minimum-norm solve into X [BH, p].  reg: [F][2] inclusive block ranges;
 // Sinv: inverse of the Schur complement [q, q], q = n - 1 + F.  Scratch: part
-// (fit_part_doubles), r [BH, p], bU [BH, q], u [kSolveSplit, BH, q].
-size_t fit_part_doubles(int BH, int n);
+// (fit_part_doubles; 0 for maps that one launch fits), r [BH, p], bU [BH, q],
+// u [kSolveSplit, BH, q].
+size_t fit_part_doubles(int BH, int n, int F);
 hipError_t launch_fit(double* G, bool logits, const int* reg, const double* Sinv, double* part, double* r, double* bU,
                       double* u, double* X, int BH, int L, int bs, int n, int F, hipStream_t s);
 

@@ -1361,7 +1361,12 @@ static int sum_rows(int BH, int n) {
     return R;
 }
 
-size_t fit_part_doubles(int BH, int n) {
+// The fit's launch holds a head's whole map in LDS: with up to NC blocks and
+// frames, NC = 64 or 128 (0: neither).
+static int small_fit(int n, int F) { return std::max(n, F) <= 64 ? 64 : (std::max(n, F) <= 128 ? 128 : 0); }
+
+size_t fit_part_doubles(int BH, int n, int F) {
+    if (small_fit(n, F)) return 0;
     const int R = sum_rows(BH, n);
     return (size_t)BH * cdiv(n, R) * (2 * (size_t)n + R - 1);
 }
@@ -1373,8 +1378,9 @@ hipError_t launch_fit(double* G, bool logits, const int* reg, const double* Sinv
         hipLaunchKernelGGL(kern, dim3((unsigned)BH), dim3(kFitThreads), 0, s, G, reg, Sinv, X, L, bs, n, F);
         return hipGetLastError();
     };
-    if (n <= 64 && F <= 64) return logits ? small(fit_small_kernel<64, true>) : small(fit_small_kernel<64, false>);
-    if (n <= 128 && F <= 128) return logits ? small(fit_small_kernel<128, true>) : small(fit_small_kernel<128, false>);
+    if (small_fit(n, F) == 64) return logits ? small(fit_small_kernel<64, true>) : small(fit_small_kernel<64, false>);
+    if (small_fit(n, F) == 128)
+        return logits ? small(fit_small_kernel<128, true>) : small(fit_small_kernel<128, false>);
 
     const int q = n - 1 + F, R = sum_rows(BH, n), nch = (int)cdiv(n, R);
     hipError_t e = hipErrorInvalidValue;

@@ -110,3 +110,16 @@ def test_fit_of_wide_maps(F, T):
     bound = 3 * n * 1e-9 * np.abs(X).max()
     assert np.abs(O.rhs(G - O.reconstruct(X, n, regions), regions)).max() <= bound
     assert abs(X @ O.null_vector(n, F)) <= bound
+
+
+def test_handle_memory_of_short_maps():
+    """A handle of short maps owns what the header states, and none of the long
+    maps' row-chunk sums (284 MB here)."""
+    H, n, d = 16384, 128, 64
+    T = n * 64 // 2
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with M.Stats(M.make_shape(1, H, 2 * T, d, 64, T), M.make_params(warmup_m=1)):
+        used = free - torch.cuda.mem_get_info()[0]
+    stated = H * (2 * n * d + n * n + 29 * n) * 8
+    assert abs(used - stated) < 128 << 20, (used, stated)
