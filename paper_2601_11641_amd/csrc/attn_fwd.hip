@@ -247,14 +247,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 //   lists  per XCD, the items of its ranges in head-major order (a chunk
 //          item is the slot number with bit 30 set), its length, start and
 //          a zeroed fetch counter; each list is then bucket-sorted by
-//          decreasing cost (lists longer than kPlanSortMax keep the head
-//          order), so long items start early instead of ending the launch
-//          late.
+//          decreasing cost, in head order within a bucket (lists longer than
+//          kPlanSortMax keep the head order), so long items start early
+//          instead of ending the launch late.
 // Every work-group computes the same split decision and slot numbering from
-// the same counts, so the plan is deterministic; only the order of equal-
-// cost items within a bucket varies, which affects timing, not results.
-// The attention work-groups are persistent (one per CU, or as many as are
-// resident of the kernel for smaller tiles): a work-group
+// the same counts, so the plan is deterministic (but for the order of the 64
+// equal-cost items that one wave places at once, which affects timing only).
+// The attention work-groups are persistent (one per CU): a work-group
 // fetches the next item of its XCD's list with an atomic counter and, once
 // that list is drained, of the other XCDs' lists, until all are drained.
 // Each counter has a 128-byte line of its own, so the XCDs' atomics do not
@@ -339,8 +338,8 @@ __device__ T plan_scan(T v, T* buf, T& total) {
 
 // Sums over all pairs are 32-bit (Acc) while they fit, and nothing of the
 // split is computed when no pair is dear enough: the passes are chains of
-// integer instructions in 16 waves (11,820 pairs: 44 us with 64-bit sums,
-// 33 us; 13 us at 1395 pairs).
+// integer instructions in 16 waves (11,820 pairs: 44 us with 64-bit sums and
+// an unordered sort, 33 us; 12 us at 1395 pairs).
 template <class Acc>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __restrict__ kv_cnt, void* ws,
                                                             int BH, int n, int ncu, int S) {
@@ -615,15 +614,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
             pl.misc[2] = all;
         }
     }
-    // Longest items first: a bucket sort of the list by decreasing cost
-    // (order within a bucket unspecified; the order only affects timing.
-    // Head order within a bucket gained nothing, 40 heads of 591 blocks with
-    // 30 kept 5.36 ms either way, and lost 5% where a split leaves just over
-    // three rounds of equal items, 4 heads of 195 blocks with 176 kept: 1.28
-    // and 1.35 ms).
+    // Longest items first: a bucket sort of the list by decreasing cost, in
+    // head order within a bucket (the order only affects timing: items of
+    // equal cost out of head order lose K/V locality, 0.7% of a launch whose
+    // rows all keep 30 of 591 blocks).  Each wave takes a contiguous part of
+    // the list and has its own cursors.
     if (lenx > kPlanSortMax) return;
     __shared__ int vals[kPlanSortMax];
-    __shared__ int cursor[kPlanBuckets];
+    constexpr int PW = kPlanThreads / 64;
+    __shared__ int cursor[PW][kPlanBuckets];
     int shift = 0;
     while (((4 + 2 * n) >> shift) >= kPlanBuckets) ++shift;
     auto bucket = [&](int item) {
@@ -637,25 +636,34 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         }
         return (kPlanBuckets - 1) - min(kPlanBuckets - 1, c >> shift);   // descending cost
     };
-    for (int bb = t; bb < kPlanBuckets; bb += kPlanThreads) cursor[bb] = 0;
+    for (int bb = t; bb < PW * kPlanBuckets; bb += kPlanThreads) cursor[bb / kPlanBuckets][bb % kPlanBuckets] = 0;
     __syncthreads();   // also: every item (and chunk) of the list has been written
-    for (int a = t; a < lenx; a += kPlanThreads) {
+    const int wv = t >> 6, part = (lenx + kPlanThreads - 1) / kPlanThreads * 64;
+    const int a0 = wv * part + (t & 63), a1 = min(lenx, (wv + 1) * part);
+    for (int a = a0; a < a1; a += 64) {
         const int it = pl.items[first + a];
         vals[a] = it;
-        atomicAdd(&cursor[bucket(it)], 1);
+        atomicAdd(&cursor[wv][bucket(it)], 1);
     }
     __syncthreads();
-    {   // exclusive scan of the bucket sizes (kPlanBuckets <= kPlanThreads entries)
+    {   // exclusive scan of the bucket sizes (one bucket per thread), then of the waves' shares
         static_assert(kPlanBuckets <= kPlanThreads, "one bucket per thread");
-        const int c = t < kPlanBuckets ? cursor[t] : 0;
-        int all = 0;
-        const int ex = plan_scan<int>(c, scan32, all);
-        if (t < kPlanBuckets) cursor[t] = ex;
+        int c = 0, all = 0;
+        if (t < kPlanBuckets)
+            for (int ww = 0; ww < PW; ++ww) c += cursor[ww][t];
+        int ex = plan_scan<int>(c, scan32, all);
+        if (t < kPlanBuckets) {
+            for (int ww = 0; ww < PW; ++ww) {
+                const int share = cursor[ww][t];
+                cursor[ww][t] = ex;
+                ex += share;
+            }
+        }
     }
     __syncthreads();
-    for (int a = t; a < lenx; a += kPlanThreads) {
+    for (int a = a0; a < a1; a += 64) {
         const int it = vals[a];
-        pl.items[first + atomicAdd(&cursor[bucket(it)], 1)] = it;
+        pl.items[first + atomicAdd(&cursor[wv][bucket(it)], 1)] = it;
     }
 }
 
