@@ -247,13 +247,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 //   lists  per XCD, the items of its ranges in head-major order (a chunk
 //          item is the slot number with bit 30 set), its length, start and
 //          a zeroed fetch counter; each list is then bucket-sorted by
-//          decreasing cost, in head order within a bucket (lists longer than
-//          kPlanSortMax keep the head order), so long items start early
-//          instead of ending the launch late.
+//          decreasing cost, in head order within a bucket, chunk by chunk
+//          (lists longer than kPlanSortMax keep the head order), so long items
+//          start early instead of ending the launch late.
 // Every work-group computes the same split decision and slot numbering from
 // the same counts, so the plan is deterministic (but for the order of the 64
 // equal-cost items that one wave places at once, which affects timing only).
-// The attention work-groups are persistent (one per CU): a work-group
+// The attention work-groups are persistent (one per CU, or as many as are
+// resident of the kernel for smaller tiles): a work-group
 // fetches the next item of its XCD's list with an atomic counter and, once
 // that list is drained, of the other XCDs' lists, until all are drained.
 // Each counter has a 128-byte line of its own, so the XCDs' atomics do not
@@ -277,7 +278,7 @@ struct Plan {
     int* misc;          // [0] split pairs, [1] chunk length in steps (0: none), [2] items
     long long* headpre; // [8][BH + 1] per work-group: cost before each head's first pair
     int* items;         // [BH * npairs + S]
-    int4* chunks;       // [S] chunk items: {pair, first step, end step, 0}
+    int4* chunks;       // [S] chunk items: {pair, first step, end step, chunk of the pair}
     int4* splits;       // [S] split pairs: {pair, chunks, first slot, 0}
     float* part;        // [S] slots of partial results
     __host__ __device__ static size_t ints(int BH, int npairs, int S) {
@@ -339,10 +340,10 @@ __device__ T plan_scan(T v, T* buf, T& total) {
 // Sums over all pairs are 32-bit (Acc) while they fit, and nothing of the
 // split is computed when no pair is dear enough: the passes are chains of
 // integer instructions in 16 waves (11,820 pairs: 44 us with 64-bit sums and
-// an unordered sort, 33 us; 12 us at 1395 pairs).
+// an unordered sort, 33 us; 13 us at 1395 pairs).
 template <class Acc>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __restrict__ kv_cnt, void* ws,
-                                                            int BH, int n, int ncu, int S) {
+                                                            int BH, int n, int ncu, int S, int by_chunk) {
     __shared__ Acc scanw[kPlanThreads / 64];
     __shared__ int scan32[kPlanThreads / 64];
     __shared__ int xcnt[kXcds];
@@ -592,7 +593,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
                 if (xq == x) {
                     pl.splits[sidx] = make_int4(q, C, slot, 0);
                     for (int cc = 0; cc < C; ++cc) {
-                        pl.chunks[slot + cc] = make_int4(q, cc * steps / C, (cc + 1) * steps / C, 0);
+                        pl.chunks[slot + cc] = make_int4(q, cc * steps / C, (cc + 1) * steps / C, cc);
                         pl.items[pos++] = kChunkBit | (slot + cc);
                     }
                 }
@@ -616,9 +617,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     }
     // Longest items first: a bucket sort of the list by decreasing cost, in
     // head order within a bucket (the order only affects timing: items of
-    // equal cost out of head order lose K/V locality, 0.7% of a launch whose
-    // rows all keep 30 of 591 blocks).  Each wave takes a contiguous part of
-    // the list and has its own cursors.
+    // equal cost out of head order lose K/V locality, 0.5-1.3% of a launch
+    // whose rows all keep 30 of 591 blocks).  The first chunks of split pairs
+    // come before the second ones, and so on (by_chunk): neighbours in the list walk
+    // the same part of K and V (4 heads of 195 blocks, 176 kept, in two chunks
+    // each: 1.39 ms with the chunks of a pair side by side, 1.32 without an
+    // order, 1.20 so); by_chunk 0 leaves a pair's chunks together, which is the
+    // better order where two groups share a unit (the same at d = 64: 0.70
+    // against 0.75 ms).  Each wave takes a contiguous part of the list and has
+    // its own cursors.
     if (lenx > kPlanSortMax) return;
     __shared__ int vals[kPlanSortMax];
     constexpr int PW = kPlanThreads / 64;
@@ -629,7 +636,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         int c;
         if (item & kChunkBit) {
             const int4 ch = pl.chunks[item & (kChunkBit - 1)];
-            c = 4 + 2 * (ch.z - ch.y);
+            c = max(0, 4 + 2 * (ch.z - ch.y) - by_chunk * ch.w);
         } else {
             const Pair pc = counts(item);
             c = 4 + pc.c0 + pc.c1;
@@ -1879,11 +1886,13 @@ hipError_t launch(const uint16_t* q, const uint16_t* k, const uint16_t* v, const
         attend(std::true_type{}, (unsigned)((P + kXcds - 1) / kXcds * kXcds));
         return hipGetLastError();
     }
+    const int by_chunk = kGroupsPerCu<D, BS> == 1;
     if (P * (4 + 2L * n) < (1L << 31))
-        hipLaunchKernelGGL(plan_kernel<int>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S);
+        hipLaunchKernelGGL(plan_kernel<int>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots, S,
+                           by_chunk);
     else
         hipLaunchKernelGGL(plan_kernel<long long>, dim3(kXcds), dim3(kPlanThreads), 0, s, kv_cnt, ws, BH, n, slots,
-                           S);
+                           S, by_chunk);
     attend(std::false_type{}, (unsigned)std::min<long>(slots, P + S));
     if (S > 0)
         hipLaunchKernelGGL((merge_kernel<D, BS>), dim3((unsigned)(2 * ncu)), dim3(256), 0, s, ws, BH, n, S, L, o,
