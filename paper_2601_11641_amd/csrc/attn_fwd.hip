@@ -971,7 +971,7 @@ __device__ __forceinline__ void store_row(const f32x16 (&oacc)[D / 32], float m,
 }
 
 // Work-groups resident on a compute unit at once: one of attn_fwd_kernel
-// (139 KB of LDS, all registers), and of attn_narrow_kernel as many as its
+// (148 KB of LDS, all registers), and of attn_narrow_kernel as many as its
 // tile buffers and the 8 KB union list allow (72 KB at 128 x 64 and 64 x 128:
 // two; 40 KB at 64 x 64: four).
 template <int D, int BS>
@@ -1505,20 +1505,24 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
 // 512 of products), so the vector unit bounds the kernel and a phase barrier
 // only adds waits; with 64-row blocks a work-group has one wave per SIMD, and
 // phases of half a tile are as short as their barriers.  Here a wave computes
-// a unit of 32 RT kv rows from start to end (scores, softmax step, product
-// with V), keeping no scores across units, which fits 128 registers at
-// d = 64: four waves share a SIMD there (two at d = 128) and cover each
-// other's matrix and LDS latencies.  Tiles are double-buffered, a whole tile
+// a unit of 32 RT kv rows from start to end (scores, then per half tile a
+// softmax step and its product with V), keeping no scores across units.  At
+// d = 64 that takes 128 registers, so that four waves share a SIMD (two at
+// d = 128) and cover each other's matrix and LDS latencies; with 128-row
+// blocks a few per-item values do not fit and lie in scratch (40 bytes per
+// lane, 32 in the direct launch, read back once per tile).  Tiles are double-buffered, a whole tile
 // ahead in the shared part, half a tile in the exclusive part (where each
 // group has half of the buffers), with one barrier per tile or half tile.
 //
 // Measured at 20% kept blocks against attn_fwd_kernel in these forms (one
 // work-group per compute unit): d = 64, block 128, 2 x 30 heads, 29,666
-// tokens 3.50 -> 2.95 ms (0.97 PFLOP/s kept); d = 128, block 64, 24 heads,
-// 35,200 tokens 4.53 -> 3.10 ms (1.04 PFLOP/s; 3.65 ms with two ping-pong
-// groups per unit).  Counters at d = 64: vector unit busy 80% and matrix
-// cores 51% of the cycles, the clock power-limited; address arithmetic for
-// the operand reads, before their offset fields held it, cost 5%.
+// tokens 3.50 -> 2.94 ms (0.98 PFLOP/s kept); d = 128, block 64, 24 heads,
+// 35,200 tokens 4.52 -> 3.17 ms (1.02 PFLOP/s; 3.65 ms with two ping-pong
+// groups per unit).  With 64-row blocks a step of 64 rows instead of two of 32
+// took 3.11 ms, but made a row's rounding depend on its pair.  Counters: vector
+// unit busy 75% and matrix cores 55% of the cycles at d = 64, 44% and 56% at
+// d = 128, the clock power-limited; address arithmetic for the operand reads,
+// before their offset fields held it, cost 5%.
 // ---------------------------------------------------------------------------
 template <int D, int BS>
 constexpr int kNarrowWaves = D == 64 ? 4 : 2;   // waves per SIMD

@@ -173,9 +173,10 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(const uint16_t* __restri
 // [l % 16], and holds D[l / 16 + 4 e][l % 16] in element e of its result.
 // T = 64 keeps five waves per SIMD (one group's stores run beside another's
 // products); T = 32 where that would leave compute units without work.  24
-// heads of 929 blocks, d = 128: 136 us with 128 x 128 tiles (two waves per
-// SIMD, whose stores all came at the same time), 117 us with 64 x 64 (45
-// TFLOP/s; an fp64 matrix product of the library runs at 72).
+// heads of 929 blocks, d = 128, predictions back to back: 136 us with 128 x 128
+// tiles (two waves per SIMD, whose stores all came at the same time), 118 us
+// with 64 x 64 (45 TFLOP/s; an fp64 matrix product of the library runs at 72);
+// within a layer step, after the attention, 132 us (40 TFLOP/s).
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -325,8 +326,9 @@ __device__ inline double quotient(double p, double s, double inv) {
 // chunk's part of the right-hand side r = M^T vec(G).  One pass over the map
 // instead of three (softmax, diagonals, columns); every sum has a fixed order.
 // Bound by the fp64 exponentials and the map's traffic: 24 heads of 929
-// blocks (166 MB) 76 us within a layer step, against 77 + 76 us for a softmax
-// pass and a pass with one thread per diagonal or column.
+// blocks (166 MB) 76 us within a layer step (67 us in predictions back to
+// back), against 77 + 76 us for a softmax pass and a pass with one thread per
+// diagonal or column.
 // ---------------------------------------------------------------------------
 template <int EPT, bool SOFTMAX>
 __global__ __launch_bounds__(kThreads) void map_sums_kernel(double* __restrict__ G, double* __restrict__ part,
@@ -849,7 +851,7 @@ __global__ void gate_kernel(const double* __restrict__ Xa, const double* __restr
 // The lane's block number is made opaque once per row: the lane masks of the
 // range and forced tests, kept across rows, spilled scalar registers from 448
 // (MASS) and 640 (TOPK) blocks on.
-// With the extrapolation: TOPK, 40 heads of 591 blocks 83 -> 41 us; MASS, 24
+// With the extrapolation: TOPK, 40 heads of 591 blocks 80 -> 41 us; MASS, 24
 // heads of 929 blocks 139 -> 71 us; bound by vector issue.  SHARED, 8 heads of
 // 2600: TOPK 290 -> 147, MASS 485 -> 259 us (a wave per row: 137 and 273); one
 // head of 4096: TOPK 71 -> 60, MASS 113 -> 105 us (82 and 147).
@@ -900,9 +902,10 @@ struct RowGrid {
 
 RowGrid row_grid(int BH, int n, int ldn, int tb0) {
     // One row per wave until that fills the chip's 1024 SIMDs eight deep;
-    // beyond, two, the second starting from the first one's boundary (23,640
-    // TOPK rows: 52 us with one, 44 with two, 44 with four, 54 with eight;
-    // 22,296 MASS rows in the whole prediction: 681, 658, 665 and 701 us).
+    // beyond, two, the second starting from the first one's boundary (40 heads
+    // of 591 blocks, TOPK 25%: 47 us with one, 41 with two, 41 with four, 45
+    // with eight; 24 of 929, MASS: 96, 79, 79 and 85 us with spilled masks, 71
+    // and 72 us with two and four without).
     const long rows = (long)BH * n;
     const int rpw = (int)std::max<long>(1, std::min<long>(kMaxRowsPerWave, rows / 4096));
     const int chunks = (n + kWavesPerGroup * rpw - 1) / (kWavesPerGroup * rpw);
