@@ -1517,10 +1517,10 @@ __global__ __launch_bounds__(BS * 4, 1) void attn_fwd_kernel(
 // Measured at 20% kept blocks against attn_fwd_kernel in these forms (one
 // work-group per compute unit): d = 64, block 128, 2 x 30 heads, 29,666
 // tokens 3.50 -> 2.94 ms (0.98 PFLOP/s kept); d = 128, block 64, 24 heads,
-// 35,200 tokens 4.52 -> 3.17 ms (1.02 PFLOP/s; 3.65 ms with two ping-pong
+// 35,200 tokens 4.52 -> 3.09 ms (1.04 PFLOP/s; 3.65 ms with two ping-pong
 // groups per unit).  With 64-row blocks a step of 64 rows instead of two of 32
-// took 3.11 ms, but made a row's rounding depend on its pair.  Counters: vector
-// unit busy 75% and matrix cores 55% of the cycles at d = 64, 44% and 56% at
+// took 3.05 ms, but made a row's rounding depend on its pair.  Counters: vector
+// unit busy 75% and matrix cores 54% of the cycles at d = 64, 45% and 57% at
 // d = 128, the clock power-limited; address arithmetic for the operand reads,
 // before their offset fields held it, cost 5%.
 // ---------------------------------------------------------------------------

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(const uint16_t* __restri
 // heads of 929 blocks, d = 128, predictions back to back: 136 us with 128 x 128
 // tiles (two waves per SIMD, whose stores all came at the same time), 118 us
 // with 64 x 64 (45 TFLOP/s; an fp64 matrix product of the library runs at 72);
-// within a layer step, after the attention, 132 us (40 TFLOP/s).
+// within a layer step, after the attention, 129-132 us (40-41 TFLOP/s).
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
